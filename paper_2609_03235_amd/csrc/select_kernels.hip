@@ -14,7 +14,10 @@
 // to tau in position order. Histograms use integer atomics only; everything
 // else is fixed-order, so results are bitwise reproducible.
 //
-// Kernels (grid y = segment b*Hkv + h):
+// Segments of up to 32768 scored keys are pooled and selected in one launch, a workgroup per
+// segment (select_segment); longer ones, and calls that want scores only, take the passes.
+//
+// Kernels (grid y = segment b*Hkv + h; select_segment: grid x):
 //   select_init    zero the histograms, write the offsets (when the column-sum pass,
 //                  which otherwise does it, does not run)
 //   radix_pass<p>  digit-p histogram of candidates matching the digits
@@ -405,6 +408,410 @@ __global__ __launch_bounds__(kBlock) void compact_kernel(CompressArgs a) {
   }
 }
 
+// Pooling, selection and compaction of a whole segment in one workgroup, for segments of up to
+// CAP scored keys: the same pooled scores (same additions in the same order) and the same kept
+// rows as the passes above, without their launches and their trips through memory.
+//   Thread t owns the E = 4*nq consecutive positions from t*E, nq odd, so that neither its
+// 16-byte reads of the staged column sums nor the write-back of its scores (stored to memory in
+// order from there) meet in LDS banks. It keeps its scores' patterns in registers; positions that
+// are no candidates get a pattern one below the segment's smallest candidate.
+//   The k-th largest is found over the candidates' own range: each pass histograms the top 11
+// bits left of (o - lo) in the current range, picks the digit and continues inside its bin, at most
+// three passes (two when the scores spread over a few percent). Subtracting lo spreads crowded
+// scores over the bins. Bound by one compute unit's vector issue and the LDS at 32K (about 2 us of
+// staging, 3 pooling, 5 the first histogram, 3 writing the scores), by its barriers and scans below.
+//   Where the segments are few, `parts` workgroups each select the whole segment (the compute
+// units are idle otherwise) and each writes a share of the scores and of the kept positions.
+//   Compaction: one block-wide scan of the threads' counts above and equal to tau; each thread
+// then puts its kept positions in order into LDS, from where they are written out together.
+constexpr int kSegBlock = 1024, kSegWaves = kSegBlock / 64;
+constexpr int kSegScoredMax = 32768;  // scored keys of a segment that fit
+constexpr int kSegDigit = 11, kSegBins = 1 << kSegDigit;
+
+// Inclusive prefix sum over the wave's lanes.
+__device__ __forceinline__ uint32_t wave_scan(uint32_t v) {
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xF, 0xF, false);  // row_shr:1
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xF, 0xF, false);  // row_shr:2
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xF, 0xF, false);  // row_shr:4
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xF, 0xF, false);  // row_shr:8
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xA, 0xF, false);  // lane 15/47 -> rows 1, 3
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xC, 0xF, false);  // lane 31 -> rows 2, 3
+  return v;
+}
+
+// Minimum of x and maximum of y over the wave.
+__device__ __forceinline__ void wave_range(uint32_t& x, uint32_t& y) {
+  auto lo = [](uint32_t u, uint32_t v) { return u < v ? u : v; };
+  auto hi = [](uint32_t u, uint32_t v) { return u > v ? u : v; };
+#define SGDKV_ROR(v, c) (uint32_t) __builtin_amdgcn_update_dpp(0, (int)(v), c, 0xF, 0xF, false)
+  x = lo(x, SGDKV_ROR(x, 0x128)), y = hi(y, SGDKV_ROR(y, 0x128));
+  x = lo(x, SGDKV_ROR(x, 0x124)), y = hi(y, SGDKV_ROR(y, 0x124));
+  x = lo(x, SGDKV_ROR(x, 0x122)), y = hi(y, SGDKV_ROR(y, 0x122));
+  x = lo(x, SGDKV_ROR(x, 0x121)), y = hi(y, SGDKV_ROR(y, 0x121));
+#undef SGDKV_ROR
+  uint32_t x4[4], y4[4];
+#pragma unroll
+  for (int g = 0; g < 4; ++g) {
+    x4[g] = (uint32_t)__builtin_amdgcn_readlane((int)x, 16 * g);
+    y4[g] = (uint32_t)__builtin_amdgcn_readlane((int)y, 16 * g);
+  }
+  x = lo(lo(x4[0], x4[1]), lo(x4[2], x4[3]));
+  y = hi(hi(y4[0], y4[1]), hi(y4[2], y4[3]));
+}
+
+// v / k, correctly rounded, for k in 1, 3, .., 15 and rc = 1/k rounded: one Newton correction of
+// the quotient (equal to the division for every finite v >= 0, checked over all of them; infinities
+// and NaN take the division).
+__device__ __forceinline__ float div_small(float v, float k, float rc) {
+  const float q = v * rc;
+  return fmaf(fmaf(-q, k, v), rc, q);
+}
+
+template <int CAP, int KP>
+__global__ __launch_bounds__(kSegBlock) void select_segment_kernel(CompressArgs a) {
+  constexpr int NQ = (CAP / (4 * kSegBlock)) | 1;  // quads per thread, at most
+  constexpr int WIN = CAP + 4 * NQ + 2 * kPoolHalo + 8;
+  __shared__ __attribute__((aligned(16))) float win[WIN];  // column sums, then scores, then kept positions
+  __shared__ __attribute__((aligned(16))) uint32_t hist[3 * kSegBins];
+  __shared__ uint32_t wa[kSegWaves], wb[kSegWaves];
+  __shared__ uint32_t pick[3];
+  const int seg = blockIdx.x, part = blockIdx.y, parts = gridDim.y;  // parts divides kSegWaves
+  const int b = seg / a.Hkv, h = seg % a.Hkv;
+  const int tid = threadIdx.x, wid = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+  const int n = (int)a.n_scored, nseg = a.B * a.Hkv;
+  const int nq = ((n + 4 * kSegBlock - 1) / (4 * kSegBlock)) | 1, E = 4 * nq;
+  const int cbeg = a.s < n ? (int)a.s : n, cend = (int)(a.C - a.W);  // candidates [cbeg, cend), cend <= n
+  const uint32_t m = (uint32_t)a.m[h];
+
+  // column sums of [-r4, n + r4) (zeros outside the scored keys), row splits combined in split order
+  const int r = KP > 0 ? (KP - 1) / 2 : (a.kp - 1) / 2;
+  const int r4 = KP > 0 ? ((KP - 1) / 2 + 3) / 4 * 4 : (r + 3) / 4 * 4;  // win[i]: position i - r4
+  const bool maxg = a.agg == 1;
+  const bool aligned = (((int64_t)seg * a.n_scored) & 3) == 0 && (((int64_t)nseg * a.n_scored) & 3) == 0;
+  const int staged = n + E + 2 * r4 + 4 < WIN ? n + E + 2 * r4 + 4 : WIN;
+  if (aligned) {
+    constexpr int U = NQ;
+    for (int i0 = 0; 4 * i0 < staged; i0 += U * kSegBlock) {
+      u32x4 x[U];
+      for (int p = 0; p < a.n_rsplit; ++p) {
+        const rsrc_t cp = make_rsrc(a.colsum + ((int64_t)p * nseg + seg) * a.n_scored, (uint64_t)n * 4);
+        u32x4 y[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) y[u] = ld128(cp, (uint32_t)((4 * (i0 + tid + u * kSegBlock) - r4) * 4));
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const float f = __uint_as_float(x[u][e]), g = __uint_as_float(y[u][e]);
+            x[u][e] = p == 0 ? y[u][e] : __float_as_uint(maxg ? fmaxf(f, g) : f + g);
+          }
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int i = 4 * (i0 + tid + u * kSegBlock);
+        if (i - r4 < n && i - r4 + 3 >= n) {  // a vector that begins inside the row is loaded whole
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            if (i - r4 + e >= n) x[u][e] = 0u;
+        }
+        if (i + 3 < WIN && i < staged) *reinterpret_cast<u32x4*>(win + i) = x[u];
+      }
+    }
+  } else {
+    constexpr int U = 2 * NQ;
+    for (int i0 = 0; i0 < staged; i0 += U * kSegBlock) {
+      float x[U];
+      for (int p = 0; p < a.n_rsplit; ++p) {
+        const rsrc_t cp = make_rsrc(a.colsum + ((int64_t)p * nseg + seg) * a.n_scored, (uint64_t)n * 4);
+        float y[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) y[u] = ldf(cp, (uint32_t)((i0 + tid + u * kSegBlock - r4) * 4));
+#pragma unroll
+        for (int u = 0; u < U; ++u) x[u] = p == 0 ? y[u] : (maxg ? fmaxf(x[u], y[u]) : x[u] + y[u]);
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (i0 + tid + u * kSegBlock < staged) win[i0 + tid + u * kSegBlock] = x[u];
+    }
+  }
+  for (int i = 4 * tid; i < 3 * kSegBins; i += 4 * kSegBlock) *reinterpret_cast<u32x4*>(hist + i) = u32x4{0u, 0u, 0u, 0u};
+  __syncthreads();
+
+  const int t0 = tid * E;
+  const float fk = (float)a.kp;
+  uint32_t o[NQ][4];
+  uint32_t kmin = 0xFFFFFFFFu, kmax = 0u;
+  if constexpr (KP > 0) {
+    // four positions from taps kept in registers: the window slides by one 16-byte read per quad
+    constexpr int R = (KP - 1) / 2, R4 = (R + 3) / 4 * 4, LEAD = R4 - R, NV = (LEAD + 4 + 2 * R + 3) / 4;
+    float x[4 * NV];
+    if (t0 < n) {
+#pragma unroll
+      for (int e = 0; e < NV - 1; ++e) {
+        const f32x4 w4 = *reinterpret_cast<const f32x4*>(win + t0 + 4 * e);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) x[4 * (e + 1) + i] = w4[i];
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) {
+#pragma unroll
+      for (int p = 0; p < 4; ++p) o[q][p] = 0u;
+      if (q >= nq || t0 >= n) continue;
+#pragma unroll
+      for (int e = 0; e < NV - 1; ++e)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) x[4 * e + i] = x[4 * (e + 1) + i];
+      const f32x4 w4 = *reinterpret_cast<const f32x4*>(win + t0 + 4 * (q + NV - 1));
+#pragma unroll
+      for (int i = 0; i < 4; ++i) x[4 * (NV - 1) + i] = w4[i];
+      float v[4];
+#pragma unroll
+      for (int p = 0; p < 4; ++p) {
+        v[p] = 0.f;
+#pragma unroll
+        for (int t = 0; t < KP; ++t) v[p] += x[LEAD + p + t];
+      }
+      // sums of non-negative scores: finite unless the four of them are not
+      const bool finite = (v[0] + v[1]) + (v[2] + v[3]) < INFINITY;
+#pragma unroll
+      for (int p = 0; p < 4; ++p) o[q][p] = __float_as_uint(div_small(v[p], fk, 1.0f / (float)KP));
+      if (!__all(finite)) {
+#pragma unroll
+        for (int p = 0; p < 4; ++p) o[q][p] = __float_as_uint(v[p] / fk);
+      }
+    }
+  } else {
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) {
+#pragma unroll
+      for (int p = 0; p < 4; ++p) o[q][p] = 0u;
+      if (q >= nq || t0 >= n) continue;
+      float v[4] = {0.f, 0.f, 0.f, 0.f};
+      const float* w = win + t0 + 4 * q + (r4 - r);
+      for (int t = 0; t <= 2 * r; ++t)
+#pragma unroll
+        for (int p = 0; p < 4; ++p) v[p] += w[p + t];
+#pragma unroll
+      for (int p = 0; p < 4; ++p) o[q][p] = __float_as_uint(v[p] / fk);
+    }
+  }
+  // this part's waves and positions
+  const int w0 = part * (kSegWaves / parts), w1 = w0 + kSegWaves / parts;
+  const bool ours = wid >= w0 && wid < w1;
+  const int p0 = w0 * 64 * E < n ? w0 * 64 * E : n, p1 = w1 * 64 * E < n ? w1 * 64 * E : n;  // p0 % 4 == 0
+  if (a.scores_wanted) {
+    __syncthreads();  // every thread has read its taps
+    if (ours && t0 < n) {
+#pragma unroll
+      for (int q = 0; q < NQ; ++q)
+        if (q < nq) *reinterpret_cast<u32x4*>(win + t0 + 4 * q) = u32x4{o[q][0], o[q][1], o[q][2], o[q][3]};
+    }
+    __syncthreads();
+    const rsrc_t pr = make_rsrc(a.pooled + (int64_t)seg * a.n_scored, (uint64_t)n * 4);
+    if (aligned) {
+      for (int i = p0 + 4 * tid; i + 3 < p1; i += 4 * kSegBlock)
+        st128(pr, (uint32_t)(i * 4), *reinterpret_cast<u32x4*>(win + i));
+      for (int i = (p0 < (p1 & ~3) ? p1 & ~3 : p0) + tid; i < p1; i += kSegBlock) stf(pr, (uint32_t)(i * 4), win[i]);
+    } else {
+      for (int i = p0 + tid; i < p1; i += kSegBlock) stf(pr, (uint32_t)(i * 4), win[i]);
+    }
+  }
+
+  // initial and recent rows: their places in the segment are known
+  const int64_t seg_off = (int64_t)b * a.T_layer + a.prefix[h];
+  const int64_t seg_len = a.prefix[h + 1] - a.prefix[h];
+  const rsrc_t kp = make_rsrc(a.kept_pos + seg_off, (uint64_t)seg_len * 4);
+  for (int64_t i = part * kSegBlock + tid; i < a.s; i += parts * kSegBlock) st32(kp, (uint32_t)(i * 4), (uint32_t)i);
+  for (int64_t i = part * kSegBlock + tid; i < a.W; i += parts * kSegBlock)
+    st32(kp, (uint32_t)((seg_len - a.W + i) * 4), (uint32_t)(a.C - a.W + i));
+  if (m == 0u) return;  // uniform: no candidate is kept
+
+  const bool inner = __all(t0 >= cbeg && t0 + E <= cend);  // every position of the wave is a candidate
+  if (inner) {
+#pragma unroll
+    for (int q = 0; q < NQ; ++q)
+      if (q < nq) {
+#pragma unroll
+        for (int p = 0; p < 4; ++p) {
+          kmin = o[q][p] < kmin ? o[q][p] : kmin;
+          kmax = o[q][p] > kmax ? o[q][p] : kmax;
+        }
+      }
+  } else if (__any(t0 < cend && t0 + E > cbeg)) {
+#pragma unroll
+    for (int q = 0; q < NQ; ++q)
+      if (q < nq) {
+#pragma unroll
+        for (int p = 0; p < 4; ++p) {
+          const int j = t0 + 4 * q + p;
+          const bool cand = j >= cbeg && j < cend;
+          kmin = cand && o[q][p] < kmin ? o[q][p] : kmin;
+          kmax = cand && o[q][p] > kmax ? o[q][p] : kmax;
+        }
+      }
+  }
+  wave_range(kmin, kmax);
+  if (lane == 0) {
+    wa[wid] = kmin;
+    wb[wid] = kmax;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int w = 0; w < kSegWaves; ++w) {
+    kmin = wa[w] < kmin ? wa[w] : kmin;
+    kmax = wb[w] > kmax ? wb[w] : kmax;
+  }
+  if (kmin == 0u) {  // uniform: make room below the smallest pattern
+#pragma unroll
+    for (int q = 0; q < NQ; ++q)
+#pragma unroll
+      for (int p = 0; p < 4; ++p) o[q][p] += o[q][p] != 0xFFFFFFFFu;
+    kmin = 1u;
+    kmax += kmax != 0xFFFFFFFFu;
+  }
+  if (!inner) {
+#pragma unroll
+    for (int q = 0; q < NQ; ++q)
+#pragma unroll
+      for (int p = 0; p < 4; ++p) {
+        const int j = t0 + 4 * q + p;
+        if (!(j >= cbeg && j < cend)) o[q][p] = kmin - 1u;
+      }
+  }
+
+  // the range [lo, lo + span] holds tau; rem = rows still to place among the candidates in it
+  uint32_t lo = kmin, span = kmax - kmin, rem = m, ties = 0xFFFFFFFFu;
+  int nb = span == 0u ? 0 : 32 - __builtin_clz(span);
+  for (int pass = 0; nb > 0; ++pass) {  // uniform, at most three passes
+    const int sh = nb > kSegDigit ? nb - kSegDigit : 0;
+    uint32_t* lh = hist + pass * kSegBins;
+    // equal digits in most lanes (ties, crowded scores) would serialise the wave's adds: a look at
+    // one position decides whether the wave adds its most common digits together
+    const uint32_t d0 = (o[0][0] - lo) >> sh;
+    const bool crowded = __popcll(__ballot(d0 == (uint32_t)__builtin_amdgcn_readfirstlane((int)d0))) >= 32;
+    if (pass == 0 && inner && !crowded) {  // every position is in the range
+#pragma unroll
+      for (int q = 0; q < NQ; ++q)
+        if (q < nq) {
+#pragma unroll
+          for (int p = 0; p < 4; ++p) atomicAdd(&lh[(o[q][p] - lo) >> sh], 1u);
+        }
+    } else {
+#pragma unroll
+      for (int q = 0; q < NQ; ++q)
+        if (q < nq) {
+#pragma unroll
+          for (int p = 0; p < 4; ++p) {
+            const uint32_t off = o[q][p] - lo;  // patterns below lo wrap past the range
+            const bool in = off <= span;
+            const unsigned long long pend = __ballot(in);
+            if (pend == 0ull) continue;
+            const uint32_t bin = off >> sh;
+            unsigned long long same = 0ull;
+            if (crowded) {
+              const int leader = __builtin_ctzll(pend);
+              same = __ballot(in && bin == (uint32_t)__builtin_amdgcn_readlane((int)bin, leader));
+              if (lane == leader) atomicAdd(&lh[bin], (uint32_t)__popcll(same));
+            }
+            if (in && !((same >> lane) & 1ull)) atomicAdd(&lh[bin], 1u);
+          }
+        }
+    }
+    __syncthreads();
+    // the digit dg with S(dg) >= rem > S(dg + 1), S the suffix sums; thread t holds bins 2t, 2t+1
+    const uint32_t c0 = lh[2 * tid], c1 = lh[2 * tid + 1];
+    const uint32_t incl = wave_scan(c0 + c1);
+    const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
+    if (lane == 0) wb[wid] = total;
+    __syncthreads();
+    uint32_t sfx = total - incl + c0 + c1;  // S(2t) within the wave
+#pragma unroll
+    for (int w = 0; w < kSegWaves; ++w) sfx += w > wid ? wb[w] : 0u;
+    const uint32_t s1 = sfx - c0, s2 = s1 - c1;
+    if (sfx >= rem && s1 < rem) {
+      pick[0] = 2 * tid;
+      pick[1] = s1;
+      pick[2] = c0;
+    } else if (s1 >= rem && s2 < rem) {
+      pick[0] = 2 * tid + 1;
+      pick[1] = s2;
+      pick[2] = c1;
+    }
+    __syncthreads();
+    lo += pick[0] << sh;
+    rem -= pick[1];
+    ties = pick[2];
+    span = (1u << sh) - 1u;
+    nb = sh;
+  }
+  const uint32_t tau = lo, keep_eq = rem;  // the first keep_eq candidates equal to tau are kept
+
+  // All ties kept (nearly always: one candidate equals tau): a candidate is kept if it is at least
+  // tau. Otherwise the counts above tau (low half) and equal to it (high half) are scanned together.
+  uint32_t* list = reinterpret_cast<uint32_t*>(win);  // the scores there have been stored
+  uint32_t above = 0, eq = 0;
+  const bool all_ties = ties == keep_eq;
+  const uint32_t low = all_ties ? tau : tau + 1u;
+#pragma unroll
+  for (int q = 0; q < NQ; ++q)
+    if (q < nq) {
+#pragma unroll
+      for (int p = 0; p < 4; ++p) above += o[q][p] >= low;
+    }
+  if (!all_ties) {
+#pragma unroll
+    for (int q = 0; q < NQ; ++q)
+      if (q < nq) {
+#pragma unroll
+        for (int p = 0; p < 4; ++p) eq += o[q][p] == tau;
+      }
+  }
+  const uint32_t own = above | (eq << 16);
+  const uint32_t incl = wave_scan(own);
+  if (lane == 63) wa[wid] = incl;
+  __syncthreads();
+  uint32_t before = incl - own, first = 0, last = 0;  // kept rows before the part's waves, and with them
+#pragma unroll
+  for (int w = 0; w <= kSegWaves; ++w) {
+    if (w == w0) first = last;
+    if (w == w1 || w == kSegWaves) break;
+    before += w < wid ? wa[w] : 0u;
+    last += wa[w];
+  }
+  uint32_t er = before >> 16;
+  auto rows = [&](uint32_t c) {  // kept rows among candidates counted as c
+    const uint32_t e = c >> 16;
+    return (c & 0xFFFFu) + (e < keep_eq ? e : keep_eq);
+  };
+  const uint32_t f0 = all_ties ? first : rows(first), f1 = all_ties ? last : rows(last);
+  if (ours) {
+    uint32_t rank = (all_ties ? before : rows(before)) - f0;
+    if (all_ties) {
+#pragma unroll
+      for (int q = 0; q < NQ; ++q)
+        if (q < nq) {
+#pragma unroll
+          for (int p = 0; p < 4; ++p)
+            if (o[q][p] >= low) list[rank++] = (uint32_t)(t0 + 4 * q + p);
+        }
+    } else {
+#pragma unroll
+      for (int q = 0; q < NQ; ++q)
+        if (q < nq) {
+#pragma unroll
+          for (int p = 0; p < 4; ++p) {
+            const bool is = o[q][p] == tau;
+            if (o[q][p] > tau || (is && er < keep_eq)) list[rank++] = (uint32_t)(t0 + 4 * q + p);
+            er += is;
+          }
+        }
+    }
+  }
+  __syncthreads();
+  for (uint32_t i = f0 + tid; i < f1; i += kSegBlock) st32(kp, ((uint32_t)a.s + i) * 4u, list[i - f0]);
+}
+
 // Copies the kept K and V rows into the ragged cache. A work item is
 // kCopyRows output rows of one segment (item = seg * copy_blocks + block);
 // workgroups take items in a grid-stride loop, so the grid may be smaller
@@ -473,12 +880,42 @@ static void launch_pool(const CompressArgs& a, dim3 grid, hipStream_t st) {
   }
 }
 
+template <int CAP>
+static void launch_select_segment(const CompressArgs& a, hipStream_t st) {
+  // shares of the write-out: as many as the segments leave compute units for, at most eight (32K x 1
+  // x 4 heads: 27 us against 30 with one)
+  int parts = 1;
+  while (parts < 8 && a.B * a.Hkv * parts * 2 <= kScoreWorkgroups) parts *= 2;
+  const dim3 grid(a.B * a.Hkv, parts), blk(kSegBlock);
+  switch (a.kp) {
+    case 1: SGDKV_LAUNCH("select_segment", (select_segment_kernel<CAP, 1>), grid, blk, st, a); break;
+    case 3: SGDKV_LAUNCH("select_segment", (select_segment_kernel<CAP, 3>), grid, blk, st, a); break;
+    case 5: SGDKV_LAUNCH("select_segment", (select_segment_kernel<CAP, 5>), grid, blk, st, a); break;
+    case 7: SGDKV_LAUNCH("select_segment", (select_segment_kernel<CAP, 7>), grid, blk, st, a); break;
+    case 9: SGDKV_LAUNCH("select_segment", (select_segment_kernel<CAP, 9>), grid, blk, st, a); break;
+    case 11: SGDKV_LAUNCH("select_segment", (select_segment_kernel<CAP, 11>), grid, blk, st, a); break;
+    case 13: SGDKV_LAUNCH("select_segment", (select_segment_kernel<CAP, 13>), grid, blk, st, a); break;
+    case 15: SGDKV_LAUNCH("select_segment", (select_segment_kernel<CAP, 15>), grid, blk, st, a); break;
+    default: SGDKV_LAUNCH("select_segment", (select_segment_kernel<CAP, 0>), grid, blk, st, a); break;
+  }
+}
+
 hipError_t launch_select(const CompressArgs& a, bool scores_only, hipStream_t st) {
   const int nseg = a.B * a.Hkv;
   const dim3 blk(kBlock);
   if (a.n_col_chunks == 0) SGDKV_LAUNCH("select_init", select_init_kernel, dim3(nseg), blk, st, a);
   const dim3 hgrid(a.n_hist_chunks, nseg);
   const bool cands = a.C - a.s - a.W > 0;
+  // Whole segments per workgroup while their scores fit its LDS and registers: faster at every size
+  // and batch up to there (pooling to compaction per layer, this / the passes below: 8K x 16 x 4
+  // heads 13.8 / 39.5 us, 32K x 1 x 4 21.8 / 36.5, 32K x 8 x 4 24 / 46, 32K x 64 x 4 34 / 96,
+  // event pairs around each launch included); a 64K segment would take twice a 32K one's time,
+  // where the passes spread it over the device.
+  if (!scores_only && a.n_scored <= kSegScoredMax && (a.kp - 1) / 2 <= kPoolHalo) {
+    if (a.n_scored <= kSegScoredMax / 4) launch_select_segment<kSegScoredMax / 4>(a, st);
+    else launch_select_segment<kSegScoredMax>(a, st);
+    return hipGetLastError();
+  }
   if (scores_only || !cands) {
     if (a.n_hist_chunks > 0) launch_pool<false>(a, hgrid, st);
     if (scores_only) return hipGetLastError();

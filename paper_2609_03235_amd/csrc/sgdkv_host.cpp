@@ -638,6 +638,7 @@ sgdkv_status sgdkv_compress_layer_ex(const sgdkv_compress_desc* desc, const sgdk
   a.kept_pos = kept_pos_out;
   a.offsets = offsets_out;
   a.pooled = scores_out ? scores_out : reinterpret_cast<float*>(ws + p.off_pooled);
+  a.scores_wanted = scores_out != nullptr;
   a.lse_part = reinterpret_cast<float*>(ws + p.off_lse_part);
   a.lse2 = reinterpret_cast<float*>(ws + p.off_lse2);
   a.colsum = reinterpret_cast<float*>(ws + p.off_colsum);

@@ -69,6 +69,7 @@ struct CompressArgs {
   int32_t* kept_pos;
   int64_t* offsets;
   float* pooled;  // caller's scores_out or workspace
+  int scores_wanted;  // pooled is the caller's
   // workspace regions
   float* lse_part;  // [B*Hkv][n_lse_chunks][R][2]  (m, s) in base-2 units
   float* lse2;      // [B*Hkv][R]                   base-2 LSE of each window row

@@ -193,6 +193,30 @@ def test_pool_kernel_widths(kp):
     _check_gather(res, t["k"], t["v"], budgets)
 
 
+@pytest.mark.parametrize("n,kp,ties,fixed", [
+    (4, 7, False, (0, 32)), (255, 1, False, (4, 32)), (4095, 7, False, (4, 32)), (4097, 15, True, (4, 64)),
+    (8192, 7, True, (4, 32)), (8193, 5, False, (0, 32)), (12289, 21, True, (128, 128)), (24571, 13, True, (4, 32)),
+    (32768, 7, False, (4, 32)), (32768, 129, True, (1024, 1024)), (32769, 7, True, (4, 32))])
+def test_selection_by_segment_size(n, kp, ties, fixed):
+    """Segments of up to 32768 scored keys are selected by one workgroup (its threads' shares change
+    with the size, odd lengths leave the second segment's rows unaligned), longer ones by the radix
+    passes: kept rows must be the top-k of the scores either way, ties to the lower position. With
+    ties, two stretches of equal keys put many equal scores at the budget's edge."""
+    B, w, (s, W) = 2, 32, fixed
+    C = n + w
+    wl, t = _tiny_inputs(B=B, C=C, seed=n + kp)
+    if ties:
+        t["k"][:, :, n // 8:n // 2] = t["k"][:, :, n // 8:n // 8 + 1]
+        t["k"][:, :, n // 2 + 100:n - n // 8] = t["k"][:, :, n // 8:n // 8 + 1]
+    mid = C - s - W
+    for budgets in (np.array([s + W + mid // 3, s + W + mid - 1]), np.array([s + W, s + W + min(1, mid)])):
+        _announce(f"selection n={n} kp={kp} ties={ties} fixed={fixed} budgets={budgets.tolist()}")
+        res, orc = _compress_both(t["q_win"], t["k"], t["v"], budgets, kp=kp, s=s, W=W)
+        _check_scores(res["scores"].cpu().numpy(), orc["pooled"], f"select {n}")
+        _check_kept(res, orc, t["q_win"].shape, C, w, s, W, budgets, f"select {n}")
+        _check_gather(res, t["k"], t["v"], budgets)
+
+
 def _qwen_small(B, C, seed_layer=0, Hq=28, Hkv=4, d=128, w=64):
     wl = workloads.WORKLOADS["qwen25_32k"]
     wl = workloads.Workload(wl.key, wl.name, 1, Hq, Hkv, d, C, w, 7, 64, 128, B, "bf16", 11, "beta")
