@@ -22,6 +22,9 @@ HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = "gfx950"
 COMMON = ["-O3", "-std=c++17", "-fPIC", "-I", INCLUDE, "-I", CSRC, "-Wall", "-Wno-unused-command-line-argument"]
 DEVICE = [f"--offload-arch={ARCH}", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
+# The score kernels' inner loops interleave MFMA and vector work: the scheduler that puts instruction
+# parallelism first measured 1-2 % faster on pass 1 (1M x 4 1734 -> 1709 us, 128K x 8 425 -> 418).
+FILE_FLAGS = {"score_kernels.hip": ["-mllvm", "-amdgpu-sched-strategy=max-ilp"]}
 KERNEL_SOURCES = ["score_kernels.hip", "select_kernels.hip", "decode_kernels.hip", "decode_scratch.hip"]
 HOST_SOURCES = ["sgdkv_host.cpp", "profile.cpp"]
 
@@ -40,7 +43,7 @@ def build(verbose: bool = False) -> str:
     jobs = []
     for src in KERNEL_SOURCES:
         obj = os.path.join(BUILD_DIR, src.replace(".hip", ".o"))
-        jobs.append([HIPCC, *COMMON, *DEVICE, "-c", os.path.join(CSRC, src), "-o", obj])
+        jobs.append([HIPCC, *COMMON, *DEVICE, *FILE_FLAGS.get(src, []), "-c", os.path.join(CSRC, src), "-o", obj])
     for src in HOST_SOURCES:
         obj = os.path.join(BUILD_DIR, src.replace(".cpp", ".o"))
         jobs.append([HIPCC, *COMMON, "-ffp-contract=off", "-fno-fast-math", "-x", "c++", "-D__HIP_PLATFORM_AMD__",

@@ -143,6 +143,29 @@ __device__ __forceinline__ void subtile_mfma(const Frag<T> (&qa)[NB > 0 ? NB : 1
     for (int j = 0; j < NB; ++j) acc[j] = mma(qa[j][c], kb[c], c == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : acc[j]);
 }
 
+// One step of the pipeline: the MFMAs of the next subtile and, between them, the vector work on the
+// logits of the current one, each logit's fma, exp2 and use one MFMA apart so that none waits for
+// the one before it.
+template <typename T, int D, int NB, typename Arg, typename Use>
+__device__ __forceinline__ void subtile_step(const Frag<T> (&qa)[NB > 0 ? NB : 1][D / 32], const Frag<T> (&kb)[D / 32],
+                                             f32x4 (&nxt)[NB > 0 ? NB : 1], const f32x4 (&cur)[NB > 0 ? NB : 1],
+                                             Arg&& arg, Use&& use) {
+  constexpr int N = 4 * NB, NM = D / 32 * NB, N1 = N > 0 ? N : 1;
+  float f[N1], e[N1];
+#pragma unroll
+  for (int k = 0; k < N + 2; ++k) {
+#pragma unroll
+    for (int q = 0; q < NM; ++q)
+      if (q >= k * NM / N1 && q < (k + 1) * NM / N1) {
+        const int c = q / (NB > 0 ? NB : 1), j = q % (NB > 0 ? NB : 1);
+        nxt[j] = mma(qa[j][c], kb[c], c == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : nxt[j]);
+      }
+    if (k < N) f[k] = arg(k / 4, k % 4, cur[k / 4][k % 4]);
+    if (k >= 1 && k - 1 < N) e[k - 1] = fast_exp2(f[k - 1]);
+    if (k >= 2) use((k - 2) / 4, (k - 2) % 4, e[k - 2]);
+  }
+}
+
 template <typename T, int D>
 __device__ __forceinline__ void subtile_frags(const char* ktile, int t, int lr, int lg, Frag<T> (&kb)[D / 32]) {
   using G = TileGeom<T, D>;
@@ -153,12 +176,12 @@ __device__ __forceinline__ void subtile_frags(const char* ktile, int t, int lr, 
 
 // Hooks: begin(acc) once with the logits of the chunk's first subtile (before
 // any sub call); sub(t, s, acc) per subtile; at_barrier(t) right after tile t's
-// barrier; end_tile(t) after tile t's last subtile.
-template <typename T, int D, int NB, int TILE, bool REV = false, typename Begin, typename Sub, typename AtBarrier,
-          typename EndTile>
+// barrier. SKEW: sub(t, s, acc, nxt, kb) issues the next subtile's MFMAs itself,
+// between its vector work.
+template <typename T, int D, int NB, int TILE, bool REV, bool SKEW, typename Begin, typename Sub, typename AtBarrier>
 __device__ __forceinline__ void chunk_pipeline(char* kbuf, const rsrc_t& kr, int64_t key0, int64_t C, int64_t ntiles,
                                                int lr, int lg, const Frag<T> (&qa)[NB > 0 ? NB : 1][D / 32],
-                                               Begin&& begin, Sub&& sub, AtBarrier&& at_barrier, EndTile&& end_tile) {
+                                               Begin&& begin, Sub&& sub, AtBarrier&& at_barrier) {
   using G = TileGeom<T, D>;
   constexpr int NBX = NB > 0 ? NB : 1;
   constexpr int S = TILE / 16;
@@ -193,14 +216,16 @@ __device__ __forceinline__ void chunk_pipeline(char* kbuf, const rsrc_t& kr, int
         __syncthreads();
         at_barrier(t);
       }
-      subtile_mfma<T, D, NB>(qa, kb[(s + 1) & 1], acc[(s + 1) & 1]);
+      if constexpr (!SKEW) subtile_mfma<T, D, NB>(qa, kb[(s + 1) & 1], acc[(s + 1) & 1]);
       if (s + 2 < S)
         subtile_frags<T, D>(buf, s + 2, lr, lg, kb[s & 1]);
       else
         subtile_frags<T, D>(nbuf, s + 2 - S, lr, lg, kb[s & 1]);
-      sub(t, s, acc[s & 1]);
+      if constexpr (SKEW)
+        sub(t, s, acc[s & 1], acc[(s + 1) & 1], kb[(s + 1) & 1]);
+      else
+        sub(t, s, acc[s & 1]);
     }
-    end_tile(t);
   }
 }
 
@@ -217,17 +242,15 @@ __device__ __forceinline__ void chunk_pipeline(char* kbuf, const rsrc_t& kr, int
 // exact online update (two exp2 per logit, m = running max), reading the keys
 // from global memory. The bound leaves room for the 16 lanes of a row, which
 // share the reference and are then added as they are: 16 * 2^122 = 2^126 stays
-// finite. The tiles that reach the window block (causal mask) or
-// pass the end of the head always take that exact path. Padded rows (past R)
-// keep m = 0.
+// finite. The keys that reach the window block (causal mask) or the end of the
+// head, and those before them that fill no whole tile, are tail chunks of their
+// own (lse_tail). Padded rows (past R) keep m = 0.
 template <typename T, int D, int NB, int TILE>
-__device__ __forceinline__ void lse_exact_tile(const rsrc_t& kr, int lr, int lg, int wid, int r0, int w, int64_t tile0,
-                                            int64_t vis0, int64_t C, const Frag<T> (&qa)[NB > 0 ? NB : 1][D / 32],
-                                            float c2, float (&m)[NB > 0 ? NB : 1][4],
-                                            float (&s)[NB > 0 ? NB : 1][4]) {
+__device__ __forceinline__ void lse_exact_tile(const rsrc_t& kr, int lr, int lg, int64_t tile0,
+                                               const Frag<T> (&qa)[NB > 0 ? NB : 1][D / 32], float c2,
+                                               float (&m)[NB > 0 ? NB : 1][4], float (&s)[NB > 0 ? NB : 1][4]) {
   using G = TileGeom<T, D>;
   constexpr int NBX = NB > 0 ? NB : 1;
-  const bool masked = tile0 + TILE > vis0;
   auto load = [&](int t, Frag<T>(&kb)[D / 32]) {
 #pragma unroll
     for (int c = 0; c < G::NC; ++c)
@@ -243,15 +266,11 @@ __device__ __forceinline__ void lse_exact_tile(const rsrc_t& kr, int lr, int lg,
     load(t + 1 < TILE / 16 ? t + 1 : t, kn);  // the next subtile's keys are in flight during this one
     f32x4 acc[NBX];
     subtile_mfma<T, D, NB>(qa, kb, acc);
-    const int64_t key = tile0 + 16 * t + lr;
-    const int64_t dk64 = key < C ? key - vis0 : (int64_t)1 << 30;  // keys past the head: never visible
-    const int dk = dk64 < -(1 << 30) ? -(1 << 30) : (dk64 > (1 << 30) ? (1 << 30) : (int)dk64);
 #pragma unroll
     for (int j = 0; j < NB; ++j)
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        const int wi = (r0 + (wid + kScoreWaves * j) * 16 + 4 * lg + i) % w;  // window index of the row
-        const float y = (masked && dk > wi) ? -INFINITY : acc[j][i] * c2;
+        const float y = acc[j][i] * c2;
         const float mn = fmaxf(m[j][i], y);
         if (mn != -INFINITY) {
           s[j][i] = s[j][i] * fast_exp2(m[j][i] - mn) + fast_exp2(y - mn);
@@ -261,6 +280,79 @@ __device__ __forceinline__ void lse_exact_tile(const rsrc_t& kr, int lr, int lg,
   }
 }
 
+// Combines the 16 lanes (keys) of each row and stores the row's (m, s) of this chunk.
+template <int NB>
+__device__ __forceinline__ void lse_store(const CompressArgs& a, int seg, int chunk, int r0, int nrows, int wid,
+                                          int lane, const float (&m)[NB > 0 ? NB : 1][4],
+                                          const float (&s)[NB > 0 ? NB : 1][4]) {
+  const int lr = lane & 15, lg = lane >> 4;
+  float* part = a.lse_part + ((int64_t)seg * a.n_lse_chunks + chunk) * a.R * 2;
+  const rsrc_t pr = make_rsrc(part, (uint64_t)a.R * 2 * sizeof(float));
+#pragma unroll
+  for (int j = 0; j < NB; ++j)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const float mx = row16_max(m[j][i]);
+      const float ss = row16_sum(m[j][i] == -INFINITY ? 0.f : s[j][i] * fast_exp2(m[j][i] - mx));
+      const int row = (wid + kScoreWaves * j) * 16 + 4 * lg + i;
+      if (lr == 0 && row < nrows)
+        st64(pr, (uint32_t)((r0 + row) * 8), (uint64_t)__float_as_uint(mx) | ((uint64_t)__float_as_uint(ss) << 32));
+    }
+}
+
+// The keys of a tail chunk (at most kLseTail, from the last whole tile every window row sees to the
+// last key some row sees): all products at once, the causal mask, then one exp2 per logit against
+// the lane's own maximum. No LDS and no loop; a workgroup is bound by the latency of its queries'
+// and keys' loads. (One workgroup per segment walking all of them 16 keys at a time, each load
+// waiting for the one before, ended the launch on short prompts: pass 1 at 6K x 1 24 us, now 14.6,
+// at 2K fp32 12 us, now 9; event pairs around the launches included.)
+template <typename T, int D, int NB>
+__device__ __forceinline__ void lse_tail(const CompressArgs& a, int seg, int chunk, int r0, int nrows, int wid, int lane,
+                                         const Frag<T> (&qa)[NB > 0 ? NB : 1][D / 32], const rsrc_t& kr) {
+  using G = TileGeom<T, D>;
+  constexpr int NBX = NB > 0 ? NB : 1, S = kLseTail / 16;
+  const int64_t key0 = a.lse_tail0 + (int64_t)(chunk - a.n_lse_head) * kLseTail;
+  const int lr = lane & 15, lg = lane >> 4;
+  Frag<T> kb[S][G::NC];
+#pragma unroll
+  for (int t = 0; t < S; ++t)
+#pragma unroll
+    for (int c = 0; c < G::NC; ++c)
+      kb[t][c] = gload_frag<T>(kr, (uint32_t)((key0 + 16 * t + lr) * G::RB + (32 * c + 8 * lg) * G::EB));
+  f32x4 acc[S][NBX];
+#pragma unroll
+  for (int t = 0; t < S; ++t) subtile_mfma<T, D, NB>(qa, kb[t], acc[t]);
+  int dk[S];  // key - window position; keys past the head are never visible
+#pragma unroll
+  for (int t = 0; t < S; ++t) {
+    const int64_t key = key0 + 16 * t + lr;
+    dk[t] = key < a.C ? (int)(key - a.win0) : 1 << 30;  // tail keys lie within 2^16 of the window
+  }
+  float m[NBX][4], s[NBX][4];
+  int wj = (r0 + wid * 16 + 4 * lg) % a.w;  // window index of the lane's first row
+  const int step = (kScoreWaves * 16) % a.w;
+#pragma unroll
+  for (int j = 0; j < NB; ++j) {
+    int wi = wj;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      float y[S], mx = -INFINITY;
+#pragma unroll
+      for (int t = 0; t < S; ++t) {
+        y[t] = dk[t] > wi ? -INFINITY : acc[t][j][i] * a.c2;
+        mx = fmaxf(mx, y[t]);
+      }
+      m[j][i] = mx;
+      s[j][i] = 0.f;
+#pragma unroll
+      for (int t = 0; t < S; ++t) s[j][i] += fast_exp2(y[t] - (mx == -INFINITY ? 0.f : mx));
+      wi = wi + 1 == a.w ? 0 : wi + 1;
+    }
+    wj = wj + step >= a.w ? wj + step - a.w : wj + step;
+  }
+  lse_store<NB>(a, seg, chunk, r0, nrows, wid, lane, m, s);
+}
+
 template <typename T, int D, int NB>
 __device__ void lse_chunk(const CompressArgs& a, char* kbuf, int seg, int chunk, int r0, int nrows, int wid,
                           int lane, const Frag<T> (&qa)[NB > 0 ? NB : 1][D / 32], const rsrc_t& kr, int64_t key0,
@@ -268,7 +360,6 @@ __device__ void lse_chunk(const CompressArgs& a, char* kbuf, int seg, int chunk,
   constexpr int NBX = NB > 0 ? NB : 1;
   constexpr int TILE = kLseTile;
   const int lr = lane & 15, lg = lane >> 4;
-  const int64_t vis0 = a.win0;  // the row with window index i sees key j iff j - vis0 <= i (and j < C)
   const float c2 = a.c2;
   float m[NBX][4], s[NBX][4];
   bool real[NBX][4];
@@ -286,13 +377,9 @@ __device__ void lse_chunk(const CompressArgs& a, char* kbuf, int seg, int chunk,
 #pragma unroll
     for (int i = 0; i < 4; ++i) real[j][i] = (wid + kScoreWaves * j) * 16 + 4 * lg + i < nrows;
   reset();
-  // whole tiles every row sees (keys below both the window block and the end of the head)
-  const int64_t open_end = vis0 < a.C ? vis0 : a.C;
-  const int64_t fast_end = key_end < open_end ? key_end : open_end;
-  const int64_t nfast = fast_end > key0 ? (fast_end - key0) / TILE : 0;
-  const int64_t ntiles = (key_end - key0 + TILE - 1) / TILE;
-  if (nfast > 0) {
-    chunk_pipeline<T, D, NB, TILE>(
+  const int64_t nfast = (key_end - key0) / TILE;  // whole tiles every row sees (>= 1)
+  {
+    chunk_pipeline<T, D, NB, TILE, false, true>(
         kbuf, kr, key0, a.C, nfast, lr, lg, qa,
         [&](const f32x4(&acc)[NBX]) {
 #pragma unroll
@@ -303,13 +390,11 @@ __device__ void lse_chunk(const CompressArgs& a, char* kbuf, int seg, int chunk,
               if (real[j][i]) m[j][i] = mx;
             }
         },
-        [&](int64_t, int, const f32x4(&acc)[NBX]) {
-#pragma unroll
-          for (int j = 0; j < NB; ++j)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) s[j][i] += fast_exp2(fmaf(acc[j][i], c2, -m[j][i]));
+        [&](int64_t, int, const f32x4(&acc)[NBX], f32x4(&nxt)[NBX], const Frag<T>(&kb)[D / 32]) {
+          subtile_step<T, D, NB>(qa, kb, nxt, acc, [&](int j, int i, float x) { return fmaf(x, c2, -m[j][i]); },
+                                 [&](int j, int i, float e) { s[j][i] += e; });
         },
-        [&](int64_t) {}, [&](int64_t) {});
+        [&](int64_t) {});
     bool bad = false;
 #pragma unroll
     for (int j = 0; j < NB; ++j)
@@ -318,58 +403,32 @@ __device__ void lse_chunk(const CompressArgs& a, char* kbuf, int seg, int chunk,
     if (__any(bad)) {
       reset();
       for (int64_t t = 0; t < nfast; ++t)
-        lse_exact_tile<T, D, NB, TILE>(kr, lr, lg, wid, r0, a.w, key0 + t * TILE, vis0, a.C, qa, c2, m, s);
+        lse_exact_tile<T, D, NB, TILE>(kr, lr, lg, key0 + t * TILE, qa, c2, m, s);
     }
   }
-  for (int64_t t = nfast; t < ntiles; ++t)
-    lse_exact_tile<T, D, NB, TILE>(kr, lr, lg, wid, r0, a.w, key0 + t * TILE, vis0, a.C, qa, c2, m, s);
-  // Combine the 16 lanes (keys) of each row, then store (m, s) for the row.
-  float* part = a.lse_part + ((int64_t)seg * a.n_lse_chunks + chunk) * a.R * 2;
-  const rsrc_t pr = make_rsrc(part, (uint64_t)a.R * 2 * sizeof(float));
-#pragma unroll
-  for (int j = 0; j < NB; ++j)
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      float mm = m[j][i], ss = s[j][i];
-#pragma unroll
-      for (int o = 1; o < 16; o <<= 1) {
-        const float mo = __shfl_xor(mm, o, 64);
-        const float so = __shfl_xor(ss, o, 64);
-        const float mn = fmaxf(mm, mo);
-        const float e1 = (mm == -INFINITY) ? 0.f : fast_exp2(mm - mn);
-        const float e2 = (mo == -INFINITY) ? 0.f : fast_exp2(mo - mn);
-        ss = ss * e1 + so * e2;
-        mm = mn;
-      }
-      const int row = (wid + kScoreWaves * j) * 16 + 4 * lg + i;
-      if (lr == 0 && row < nrows) {
-        stf(pr, (uint32_t)((r0 + row) * 8), mm);
-        stf(pr, (uint32_t)((r0 + row) * 8 + 4), ss);
-      }
-    }
+  lse_store<NB>(a, seg, chunk, r0, nrows, wid, lane, m, s);
 }
 
 template <typename T, int D, int RBW>
 __global__ __launch_bounds__(kScoreBlock, 1) void lse_kernel(CompressArgs a) {
   using G = TileGeom<T, D>;
   __shared__ __attribute__((aligned(16))) char ktile[2 * kLseTile * G::LDS_STRIDE];
-  const int seg = blockIdx.y;
+  const int nseg = a.B * a.Hkv;
+  const int seg = (int)blockIdx.x % nseg, split = (int)blockIdx.x / nseg;
   const int b = seg / a.Hkv, h = seg % a.Hkv;
-  // the tail chunk (the causally masked tiles, on the exact path) goes first, then the uniform
-  // chunks of keys every row sees; keys past the last window row's position are seen by no row
-  const int chunk = (int)(gridDim.x - 1 - blockIdx.x);
-  const int64_t vis_end = a.win0 + a.w < a.C ? a.win0 + a.w : a.C;
-  int64_t key0, key_end;
-  if (chunk < a.n_lse_head) {
-    key0 = (int64_t)chunk * a.lse_chunk;
-    key_end = key0 + a.lse_chunk < a.lse_tail0 ? key0 + a.lse_chunk : a.lse_tail0;
-  } else {
-    key0 = a.lse_tail0;
-    key_end = vis_end;
-  }
-  if (key0 >= key_end) return;
+  // The uniform chunks of keys every row sees come first in the grid, then the short tail chunks, if
+  // those have workgroups of their own (with both mixed segment by segment, some shader engines got
+  // more long workgroups than they have compute units: 766 us for 420 at 128K x 8); otherwise the
+  // last uniform chunk's workgroup goes on to them. Keys past the last window row's position are
+  // seen by no row.
+  const int chunk = (int)blockIdx.y;
+  const int64_t key0 = (int64_t)chunk * a.lse_chunk;
+  const int64_t key_end = key0 + a.lse_chunk < a.lse_tail0 ? key0 + a.lse_chunk : a.lse_tail0;
+  const int tail0 = chunk >= a.n_lse_head ? chunk : a.n_lse_head;  // tail chunks of this workgroup
+  const int tail1 = chunk >= a.n_lse_head ? chunk + 1
+                    : chunk == a.n_lse_head - 1 && (int)gridDim.y == a.n_lse_head ? a.n_lse_chunks : 0;
   const int tid = threadIdx.x, wid = tid >> 6, lane = tid & 63;
-  const int r0 = (int)blockIdx.z * a.lse_rs_rows;
+  const int r0 = split * a.lse_rs_rows;
   const int nrows = a.R - r0 < a.lse_rs_rows ? a.R - r0 : a.lse_rs_rows;
   const rsrc_t kr = make_rsrc(static_cast<const T*>(a.k) + (int64_t)seg * a.C * D, (uint64_t)a.C * G::RB);
   Frag<T> qa[RBW][G::NC];
@@ -377,14 +436,18 @@ __global__ __launch_bounds__(kScoreBlock, 1) void lse_kernel(CompressArgs a) {
   // blocks this wave owns: RBW or RBW-1 (uniform per wave)
   const int nrb = (nrows + 15) / 16;
   if (wid + kScoreWaves * (RBW - 1) < nrb) {
-    lse_chunk<T, D, RBW>(a, ktile, seg, chunk, r0, nrows, wid, lane, qa, kr, key0, key_end);
+    if (chunk < a.n_lse_head)
+      lse_chunk<T, D, RBW>(a, ktile, seg, chunk, r0, nrows, wid, lane, qa, kr, key0, key_end);
+    for (int c = tail0; c < tail1; ++c) lse_tail<T, D, RBW>(a, seg, c, r0, nrows, wid, lane, qa, kr);
   } else {
     Frag<T> qb[RBW > 1 ? RBW - 1 : 1][G::NC];
 #pragma unroll
     for (int j = 0; j < RBW - 1; ++j)
 #pragma unroll
       for (int c = 0; c < G::NC; ++c) qb[j][c] = qa[j][c];
-    lse_chunk<T, D, RBW - 1>(a, ktile, seg, chunk, r0, nrows, wid, lane, qb, kr, key0, key_end);
+    if (chunk < a.n_lse_head)
+      lse_chunk<T, D, RBW - 1>(a, ktile, seg, chunk, r0, nrows, wid, lane, qb, kr, key0, key_end);
+    for (int c = tail0; c < tail1; ++c) lse_tail<T, D, RBW - 1>(a, seg, c, r0, nrows, wid, lane, qb, kr);
   }
 }
 
@@ -563,7 +626,7 @@ __device__ void colsum_chunk(const CompressArgs& a, char* kbuf, float* red, floa
     const bool store = t >= 0 && lane < CPW && key < key_end;
     stf(cr, store ? (uint32_t)(key * 4) : (uint32_t)(a.n_scored * 4), v * a.out_scale);
   };
-  chunk_pipeline<T, D, NB, TILE, true>(
+  chunk_pipeline<T, D, NB, TILE, true, false>(
       kbuf, kr, key0, a.C, ntiles, lr, lg, qa, [](const f32x4(&)[NBX]) {},
       [&](int64_t t, int sub, const f32x4(&acc)[NBX]) {
         const int t3 = (int)((uint32_t)t % 3u);  // tiles of a chunk: far fewer than 2^32
@@ -599,7 +662,7 @@ __device__ void colsum_chunk(const CompressArgs& a, char* kbuf, float* red, floa
           red[CP::at(t3, wid, lg, 16 * sub + lr)] = p;  // one partial per lane group; the reduction adds them
         }
       },
-      [&](int64_t t) { reduce(t - 1); }, [](int64_t) {});
+      [&](int64_t t) { reduce(t - 1); });
   __syncthreads();
   reduce(ntiles - 1);
 }
@@ -673,7 +736,7 @@ __global__ __launch_bounds__(kScoreBlock, 1) void colsum_kernel(CompressArgs a) 
 template <typename T, int D, int RBW>
 static hipError_t launch_lse_t(const CompressArgs& a, hipStream_t st) {
   const dim3 sblk(kScoreBlock);
-  SGDKV_LAUNCH("score_lse", (lse_kernel<T, D, RBW>), dim3(a.n_lse_chunks, a.B * a.Hkv, a.lse_n_rsplit), sblk, st, a);
+  SGDKV_LAUNCH("score_lse", (lse_kernel<T, D, RBW>), dim3(a.B * a.Hkv * a.lse_n_rsplit, a.n_lse_wgs), sblk, st, a);
   constexpr int rows_per_wg = kBlock / kMergeLanes;
   SGDKV_LAUNCH("lse_merge", lse_merge_kernel, dim3((unsigned)((a.R + rows_per_wg - 1) / rows_per_wg), a.B * a.Hkv),
                dim3(kBlock), st, a);

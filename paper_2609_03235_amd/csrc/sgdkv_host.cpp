@@ -401,36 +401,35 @@ sgdkv_status plan_compress(const sgdkv_compress_desc* d, int64_t win0, CompressP
       std::max<int64_t>(round_up(ceil_div(nseg * a.n_rsplit * a.C, sgdkv::kScoreWorkgroups), sgdkv::kScoreChunkQuantum),
                         2 * sgdkv::kScoreChunkQuantum),
       1 << 16);
-  // pass 1 covers the keys some window row sees, [0, min(C, win0 + w)), in uniform chunks (about
-  // one workgroup per CU). The chunk holding the causally masked tiles runs them on the exact
-  // path, which then ends the launch. Where that costs more than what splitting those tiles off
-  // into a short chunk of their own costs -- its workgroups (one per segment and row split, on
-  // the exact path, dispatched first) leave their CUs idle for the rest of the launch, about
-  // tiles-per-chunk x tails / (256 CUs) tile times, against about two for the exact tiles --
-  // the masked tiles get that chunk, and the uniform chunks aim at the CUs the tails leave. The
-  // chunk sizes depend on C only, so the workspace does not depend on win0.
+  // pass 1 covers the keys some window row sees, [0, min(C, win0 + w)): the whole tiles every row
+  // sees in uniform chunks (about one workgroup per CU), the rest (at most w + 127 keys) in short
+  // tail chunks. Those get workgroups of their own (about 5 us each) where they run beside the
+  // uniform chunks, at most one workgroup per CU in all, for which a uniform chunk may be a tile
+  // longer; run after them they cost the launch those 5 us (5 % at 100K x 1), so otherwise the
+  // last uniform chunk's workgroup, usually the shortest, does them. The chunk sizes depend on C and
+  // w only, so the workspace does not depend on win0.
   {
-    const int64_t tails = nseg * a.n_rsplit;
     const int64_t vis_end = std::min<int64_t>(a.C, win0 + a.w);
     const int64_t open_end = std::min<int64_t>(a.C, win0);
+    const int64_t tails_max = ceil_div(a.w + sgdkv::kLseTile - 1, sgdkv::kLseTail);
+    const int64_t tails = nseg * a.n_rsplit * tails_max;
     auto chunk_for = [&](int64_t target) {
-      return std::min<int64_t>(
-          std::max<int64_t>(round_up(ceil_div(tails * a.C, target), sgdkv::kScoreChunkQuantum),
-                            2 * sgdkv::kScoreChunkQuantum),
-          1 << 16);
+      return std::min<int64_t>(std::max<int64_t>(round_up(ceil_div(nseg * a.n_rsplit * a.C, target),
+                                                          sgdkv::kScoreChunkQuantum),
+                                                 sgdkv::kScoreChunkQuantum),
+                               1 << 16);
     };
     a.lse_chunk = chunk_for(sgdkv::kScoreWorkgroups);
-    const bool split_tail = (a.lse_chunk / sgdkv::kLseTile) * tails < 2 * sgdkv::kScoreWorkgroups &&
-                            tails < sgdkv::kScoreWorkgroups;
-    if (split_tail) {
-      a.lse_chunk = chunk_for(sgdkv::kScoreWorkgroups - tails);
-      a.lse_tail0 = open_end / sgdkv::kLseTile * sgdkv::kLseTile;
-    } else {
-      a.lse_tail0 = vis_end;  // no tail chunk: the last uniform chunk holds the masked tiles
+    if (tails < sgdkv::kScoreWorkgroups) {
+      const int64_t beside = chunk_for(sgdkv::kScoreWorkgroups - tails);
+      if (beside - a.lse_chunk <= sgdkv::kLseTile) a.lse_chunk = beside;
     }
+    a.lse_tail0 = open_end / sgdkv::kLseTile * sgdkv::kLseTile;
     a.n_lse_head = (int)ceil_div(a.lse_tail0, a.lse_chunk);
-    a.n_lse_chunks = a.n_lse_head + (vis_end > a.lse_tail0 ? 1 : 0);
-    p.lse_chunks_max = (int)ceil_div(a.C, a.lse_chunk) + 1;
+    a.n_lse_chunks = a.n_lse_head + (int)ceil_div(vis_end - a.lse_tail0, sgdkv::kLseTail);
+    const bool own = nseg * a.n_rsplit * a.n_lse_chunks <= sgdkv::kScoreWorkgroups || a.n_lse_head == 0;
+    a.n_lse_wgs = own ? a.n_lse_chunks : a.n_lse_head;
+    p.lse_chunks_max = (int)(ceil_div(a.C, a.lse_chunk) + tails_max);
   }
   a.n_col_chunks = (int)ceil_div(a.n_scored, a.score_chunk);
   // pooling, radix and compaction passes: about 1024 workgroups, of 1024 to kHistChunkMax positions

@@ -21,6 +21,7 @@ constexpr int kBlock = 256;        // threads per workgroup in every kernel but 
 constexpr int kDecodeBlock = SGDKV_DECODE_BLOCK;  // threads per decode-split workgroup: one split per wave
 constexpr int kDecodeWaves = kDecodeBlock / 64;   // splits a decode workgroup merges into one partial
 constexpr int kLseTile = 128;      // keys staged in LDS per step of score pass 1
+constexpr int kLseTail = 32;        // keys of a pass-1 tail chunk (the causally masked ones and the last part tile)
 constexpr int kColTileBf16 = 128;  // keys staged in LDS per step of score pass 2 (bf16 keys)
 constexpr int kColTileF32 = 64;    // the same for fp32 keys (LDS holds half as many)
 constexpr int kScoreChunkQuantum = 128;  // score chunks are whole tiles of both passes
@@ -90,12 +91,14 @@ struct CompressArgs {
   // chunking
   int64_t score_chunk;  // keys per pass-2 workgroup (multiple of kScoreChunkQuantum)
   // pass 1: n_lse_head chunks of lse_chunk keys over [0, lse_tail0), the keys every window row sees
-  // in whole tiles, then (if any key remains that some row sees) one chunk [lse_tail0, min(C, win0 + w))
-  // holding the causally masked tiles, which take the exact path
+  // in whole tiles, then tail chunks of kLseTail keys over [lse_tail0, min(C, win0 + w)), the
+  // causally masked keys and those before them that fill no whole tile
   int64_t lse_chunk;
   int64_t lse_tail0;
   int n_lse_head;
-  int n_lse_chunks;     // n_lse_head + the tail chunk
+  int n_lse_chunks;     // n_lse_head + the tail chunks
+  int n_lse_wgs;        // workgroups per segment and row split: n_lse_chunks, or n_lse_head where the last
+                        // uniform chunk's workgroup does the tail chunks too
   int n_col_chunks;     // ceil(n_scored / score_chunk)
   int64_t hist_chunk;   // positions per pooling / radix-pass / compaction workgroup (multiple of 256)
   int n_hist_chunks;    // ceil(n_scored / hist_chunk): scored chunks

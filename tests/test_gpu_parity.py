@@ -193,6 +193,26 @@ def test_pool_kernel_widths(kp):
     _check_gather(res, t["k"], t["v"], budgets)
 
 
+@pytest.mark.parametrize("C,w,win0,dtype", [
+    (640, 64, None, torch.bfloat16), (641, 64, 577, torch.bfloat16), (703, 63, None, torch.bfloat16),
+    (767, 64, 640, torch.bfloat16), (900, 33, 900, torch.bfloat16), (1024, 16, 1024, torch.float32),
+    (300, 200, None, torch.float32), (97, 64, 33, torch.bfloat16), (64, 63, 1, torch.float32)])
+def test_window_lse_tail_chunks(C, w, win0, dtype):
+    """Pass 1's tail chunks of 32 keys: the causally masked keys and what is left before them of a
+    whole tile, with the window at, before and after the prompt's end, lengths around the tile and
+    chunk sizes, and no whole tile at all. The pooled scores carry every row's LSE."""
+    B, Hq, Hkv, d = 2, 14, 2, 64
+    wl = workloads.Workload("tail", "tail", 1, Hq, Hkv, d, C, w, 5, 0, 0, B, "bf16", 17, "beta")
+    t = workloads.torch_layer_tensors(wl, 0, DEV, dtype=dtype)
+    P0 = C - w if win0 is None else win0
+    W = max(C - P0, 1)
+    budgets = np.array([W + (C - W) // 3, C])
+    _announce(f"lse tail C={C} w={w} win0={win0} {dtype}")
+    res, orc = _compress_both(t["q_win"], t["k"], t["v"], budgets, kp=5, s=0, W=W, win0=win0)
+    _check_scores(res["scores"].cpu().numpy(), orc["pooled"], "lse tail", rtol=_score_rtol(t["q_win"]))
+    _check_kept(res, orc, t["q_win"].shape, C, w, 0, W, budgets, "lse tail", win0=win0, rtol=_score_rtol(t["q_win"]))
+
+
 @pytest.mark.parametrize("n,kp,ties,fixed", [
     (4, 7, False, (0, 32)), (255, 1, False, (4, 32)), (4095, 7, False, (4, 32)), (4097, 15, True, (4, 64)),
     (8192, 7, True, (4, 32)), (8193, 5, False, (0, 32)), (12289, 21, True, (128, 128)), (24571, 13, True, (4, 32)),
