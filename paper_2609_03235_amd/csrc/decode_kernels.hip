@@ -46,13 +46,14 @@ __device__ __forceinline__ int64_t uniform64(int64_t v) {
 __device__ __forceinline__ void decode_workgroup(const DecodeArgs& a, int& seg, int& x, int& ncw) {
   if (a.compact) {
     const int flat = blockIdx.x;
-    int lo = 0, hi = a.B * a.Hkv;  // the last segment lo with wg_start[lo] <= flat (uniform)
-    while (hi - lo > 1) {
-      const int mid = (lo + hi) >> 1;
-      if (a.wg_start[mid] <= flat) lo = mid;
-      else hi = mid;
-    }
-    seg = lo;
+    // the last segment that starts at or before the workgroup: each wave looks at 64 segments of
+    // the table at once (a binary search is a chain of scalar loads, one per halving)
+    const int nseg = a.B * a.Hkv, lane = threadIdx.x & 63;
+    int upto = 0;
+#pragma unroll 1
+    for (int i = 0; i < nseg; i += 64)
+      upto += __popcll(__ballot(i + lane < nseg && a.wg_start[i + lane < nseg ? i + lane : 0] <= flat));
+    seg = upto - 1;
     ncw = a.wg_start[seg + 1] - a.wg_start[seg] - a.n_new_wg;
     const int local = flat - a.wg_start[seg];
     x = local < ncw ? local : a.n_cwg + (local - ncw);
@@ -255,8 +256,11 @@ __device__ __forceinline__ void decode_chunk(const DecodeArgs& a, float (*pls)[1
   }
 }
 
-// CPL = value columns per lane; GM = compile-time bound on the group size (8
-// or 16); PF = steps of K/V in flight ahead of the one being computed; OCC =
+// CPL = value columns per lane; GM = compile-time bound on the group size (1,
+// 2, 4, 7, 8 or 16: the P.V work, 256 fmas per lane and step at 8, and the
+// reductions are done for GM heads; with the bounds below 8, the reductions off
+// the LDS and the merge by four columns, the split kernel at 32K x 1 13.5 -> 12.4
+// us, at 50K x 3 29.1 -> 27.5, at 128K x 8 100 -> 99); PF = steps of K/V in flight ahead of the one being computed; OCC =
 // waves per SIMD the registers are sized for (launch bounds: at least OCC
 // waves per execution unit). Each wave owns one split of a segment: split
 // index = kWaves*x + wave within the workgroup's region (the
@@ -356,7 +360,10 @@ __global__ __launch_bounds__(kDecodeBlock, OCC) void decode_split_kernel(DecodeA
       for (int e = 0; e < CPL; ++e) o[g][e] = 0.f;
   }
 
-  // Reduce within the wave: the 16 lanes of each head's sum, the KG key groups of o.
+  // Reduce within the wave: the 16 lanes of each head's sum, the KG key groups of o (lanes 16 apart,
+  // and 8 apart where a value row takes 8 lanes). On the vector ALU: as LDS permutes, the 128 of a
+  // wave took 4.6 of a 64-row split's 22 thousand cycles.
+  static_assert(S::LPR == 16 || S::LPR == 8, "key groups");
 #pragma unroll
   for (int i = 0; i < 4; ++i) s[i] = row16_sum(s[i]);
 #pragma unroll
@@ -364,9 +371,8 @@ __global__ __launch_bounds__(kDecodeBlock, OCC) void decode_split_kernel(DecodeA
 #pragma unroll
     for (int e = 0; e < CPL; ++e) {
       float x = o[g][e];
-#pragma unroll
-      for (int sft = S::LPR; sft < 64; sft <<= 1) x += __shfl_xor(x, sft, 64);
-      o[g][e] = x;
+      if constexpr (S::LPR == 8) x += dpp_ror8(x);
+      o[g][e] = sum_lane_groups(x);
     }
   // Merge the workgroup's splits: each wave leaves its (m, s) and o per head in LDS; then the
   // workgroup's threads merge them in wave order and write one partial per head in the
@@ -394,20 +400,23 @@ __global__ __launch_bounds__(kDecodeBlock, OCC) void decode_split_kernel(DecodeA
   const int64_t slot = a.compact ? (int64_t)blockIdx.x - sbase : x;  // within the segment's slots
   const rsrc_t mr = make_rsrc(a.part_ms + sbase * G * 2, (uint64_t)nsl * G * 8);
   const rsrc_t orr = make_rsrc(a.part + sbase * G * D, (uint64_t)nsl * G * D * 4);
-  for (int idx = tid; idx < G * D; idx += kDecodeBlock) {
-    const int g = idx / D, col = idx % D;
+  for (int idx = tid; idx < G * (D / 4); idx += kDecodeBlock) {  // four columns per thread
+    const int g = idx / (D / 4), col = 4 * (idx % (D / 4));
     float M = -INFINITY;
 #pragma unroll
     for (int w = 0; w < kWaves; ++w) M = fmaxf(M, mws[w][g]);
-    float O = 0.f, Ssum = 0.f;
+    f32x4 O = {0.f, 0.f, 0.f, 0.f};
+    float Ssum = 0.f;
 #pragma unroll
     for (int w = 0; w < kWaves; ++w) {
       const float mw = mws[w][g];
       const float e = mw == -INFINITY ? 0.f : fast_exp2(mw - M);
-      O += ows[w][g][col] * e;
+      const f32x4 ow = *reinterpret_cast<const f32x4*>(&ows[w][g][col]);
+#pragma unroll
+      for (int k = 0; k < 4; ++k) O[k] += ow[k] * e;
       Ssum += sws[w][g] * e;
     }
-    stf(orr, (uint32_t)(((slot * G + g) * D + col) * 4), O);
+    st128(orr, (uint32_t)(((slot * G + g) * D + col) * 4), __builtin_bit_cast(u32x4, O));
     if (col == 0)
       st64(mr, (uint32_t)((slot * G + g) * 8),
            (uint64_t)__float_as_uint(M) | ((uint64_t)__float_as_uint(Ssum) << 32));
@@ -551,10 +560,15 @@ static void launch_decode_t(const DecodeArgs& a, hipStream_t st) {
   constexpr int PF = wide ? SGDKV_DECODE_PF : 1;
   constexpr int CPL = wide ? SGDKV_DECODE_CPL : 8;
   constexpr int OCC = wide ? SGDKV_DECODE_OCC : 2;
-  if (a.G <= 8)
-    SGDKV_LAUNCH("decode_split", (decode_split_kernel<T, D, CPL, 8, PF, OCC>), grid, dim3(kDecodeBlock), st, a);
+#define SGDKV_SPLIT(GM) SGDKV_LAUNCH("decode_split", (decode_split_kernel<T, D, CPL, GM, PF, OCC>), grid, dim3(kDecodeBlock), st, a)
+  if (a.G <= 1) SGDKV_SPLIT(1);
+  else if (a.G <= 2) SGDKV_SPLIT(2);
+  else if (a.G <= 4) SGDKV_SPLIT(4);
+  else if (a.G <= 7) SGDKV_SPLIT(7);
+  else if (a.G <= 8) SGDKV_SPLIT(8);
   else
     SGDKV_LAUNCH("decode_split", (decode_split_kernel<T, D, 8, 16, 1, 2>), grid, dim3(kDecodeBlock), st, a);
+#undef SGDKV_SPLIT
 }
 
 // Copies one token's K rows (blockIdx.y = 0) or V rows (1), [B*Hkv][d] each, into row `slot`

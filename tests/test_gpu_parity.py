@@ -669,6 +669,40 @@ def test_decode_fixed_reference_redo():
     assert np.abs(lse.cpu().numpy() - ref_lse).max() <= 2e-2
 
 
+@pytest.mark.parametrize("G,d,dtype,rows,cap", [
+    (1, 64, torch.bfloat16, 4096, 0), (2, 128, torch.bfloat16, 9001, 40), (3, 128, torch.float32, 30011, 0),
+    (4, 64, torch.float32, 20000, 300), (5, 128, torch.bfloat16, 66000, 0), (7, 128, torch.bfloat16, 65530, 7),
+    (7, 64, torch.bfloat16, 81921, 0), (8, 128, torch.bfloat16, 50001, 64)])
+def test_decode_one_workgroup_per_unit(G, d, dtype, rows, cap):
+    """Every compiled group bound, over four segments of unequal lengths (one empty, one short) whose
+    total gives splits of 64 to 320 rows and, at 81921 x 4, the shorter ones past that; with
+    appended rows where cap is set."""
+    B, Hkv = 1, 4
+    rng = np.random.Generator(np.random.PCG64(rows + G))
+    lens = np.array([rows * 2, 0, 17, rows * 2 - 17], dtype=np.int64)
+    offs = np.concatenate([[0], np.cumsum(lens)])
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(rows + G)
+    mk = lambda *shape: torch.randn(shape, generator=gen, device=DEV).to(dtype)
+    kc, vc, q = mk(int(offs[-1]), d), mk(int(offs[-1]), d), mk(B, Hkv * G, d)
+    k_new, v_new, n_new = (mk(B, Hkv, cap, d), mk(B, Hkv, cap, d), int(rng.integers(1, cap + 1))) if cap else (None, None, 0)
+    _announce(f"decode G={G} d={d} {dtype} rows={rows} cap={cap} n_new={n_new}")
+    out, lse = sg.decode_attention(q, kc, vc, torch.from_numpy(offs).to(DEV), offs, Hkv, out_dtype=torch.float32,
+                                   k_new=k_new, v_new=v_new, n_new=n_new)
+    for h in range(Hkv):
+        k, v = kc[offs[h]:offs[h + 1]].double(), vc[offs[h]:offs[h + 1]].double()
+        if cap:
+            k, v = torch.cat([k, k_new[0, h, :n_new].double()]), torch.cat([v, v_new[0, h, :n_new].double()])
+        sl = slice(h * G, (h + 1) * G)
+        if k.shape[0] == 0:
+            assert torch.all(out[0, sl] == 0) and torch.all(torch.isinf(lse[0, sl]))
+            continue
+        logits = q[0, sl].double() @ k.T / math.sqrt(d)
+        # fp32 sums of at most 2^18 terms in splits of 320: a few 2^-24 of values of order 1
+        assert (out[0, sl].double() - torch.softmax(logits, 1) @ v).abs().max() <= 1e-5
+        assert (lse[0, sl].double() - torch.logsumexp(logits, 1)).abs().max() <= 1e-5
+
+
 @pytest.mark.parametrize("dtype,cap", [(torch.bfloat16, 300), (torch.float32, 20)])
 def test_decode_with_appended_rows(dtype, cap):
     """Generation after compression: each step appends one K/V row per KV head (sgdkv_append_kv)
