@@ -696,6 +696,7 @@ namespace {
 #endif
 constexpr int64_t kDecodeSplits = SGDKV_DECODE_SPLITS;
 constexpr int64_t kDecodeMinChunk = SGDKV_DECODE_MIN_CHUNK;
+constexpr int64_t kDecodeUnitChunk = 320;  // longest splits that are chosen to launch one workgroup per unit
 constexpr bool kDecodeWholeRounds = SGDKV_DECODE_WHOLE_ROUNDS != 0;
 // decode workgroups the MI355X runs at once: two per compute unit (their registers), 256 units
 constexpr int64_t kDecodeResident = 2 * sgdkv::kScoreWorkgroups;
@@ -802,18 +803,29 @@ sgdkv_status plan_decode(const sgdkv_decode_desc* d, const int64_t* offsets_host
   // kDecodeMinChunk rows; one round of longer splits measured slower
   a.chunk = std::min<int64_t>(
       std::max<int64_t>(round_up(ceil_div(total - offsets_host[0], kDecodeSplits), 64), kDecodeMinChunk), 1 << 24);
-  // a batch whose minimum-size splits would launch fewer workgroups than the device has compute
-  // units gets splits half as long (64 rows measured best at 32K x B 1: shorter ones add more
-  // partials to combine than they save); one that would launch more than two rounds of them gets
-  // splits twice as long (fewer workgroups, each with less of its fixed cost per row, and fewer
-  // partials to combine: decode per 128K x B 8 layer -3.7 %; the 256K x B 16 and 1M x B 32 caches
-  // already have splits of 512 rows and more)
+  // A cache small enough gets the shortest splits (of at least 64 rows) that launch at most one
+  // workgroup per compute unit, with room for one of appended rows per segment (up to 32; whatever the
+  // capacity, so that a call without appended rows does not depend on it): two workgroups on one unit take nearly twice as long as one, and 64-row splits at any
+  // count (or 128-row ones past 256 workgroups) left units with two beside units with one. Decode per
+  // call, so chosen / as before: 143K rows 20.6 / 28.2 us, 168K 24.9 / 31.4, 106K 19.3 / 23.7, 264K 31.0 / 35.5,
+  // 318K 33.0 / 36.3. Past 320 rows a split two rounds of shorter ones are as fast (287K rows: 288
+  // rows 35.4, 320 31.3, two rounds 33.9). Below 64 rows the partials to combine cost more than
+  // the shorter splits save (39K rows: 48 rows 15.0, 64 14.5).
+  // One that would launch more than two rounds gets splits twice as long (fewer workgroups, each with
+  // less of its fixed cost per row, and fewer partials to combine: decode per 128K x B 8 layer -3.7 %;
+  // the 256K x B 16 and 1M x B 32 caches already have splits of 512 rows and more)
   const int wpw = sgdkv::kDecodeWaves;  // splits (waves) per decode workgroup
   if (a.chunk == kDecodeMinChunk) {
-    int64_t wgs = 0;
-    for (int64_t i = 0; i < nseg; ++i) wgs += ceil_div(ceil_div(offsets_host[i + 1] - offsets_host[i], a.chunk), wpw);
-    if (wgs < sgdkv::kScoreWorkgroups) a.chunk = kDecodeMinChunk / 2;
-    else if (wgs > 2 * kDecodeResident) a.chunk = kDecodeMinChunk * 2;
+    auto workgroups = [&](int64_t chunk) {
+      int64_t n = 0;
+      for (int64_t i = 0; i < nseg; ++i) n += ceil_div(ceil_div(offsets_host[i + 1] - offsets_host[i], chunk), wpw);
+      return n;
+    };
+    const int64_t units = sgdkv::kScoreWorkgroups - std::min<int64_t>(nseg, sgdkv::kScoreWorkgroups / 8);
+    int64_t c = std::max<int64_t>(round_up(ceil_div(total - offsets_host[0], units * wpw), 16), kDecodeMinChunk / 2);
+    while (c <= kDecodeUnitChunk && workgroups(c) > units) c += 16;
+    if (c <= kDecodeUnitChunk) a.chunk = c;
+    else if (workgroups(a.chunk) > 2 * kDecodeResident) a.chunk = kDecodeMinChunk * 2;
   }
   a.n_chunk_max = (int)ceil_div(longest, a.chunk);
   if ((int64_t)a.B * a.Hkv * capacity * rb > 0xFFFFFFFFll)
