@@ -745,11 +745,11 @@ __global__ __launch_bounds__(kScoreBlock, 1) void colsum_kernel(CompressArgs a) 
 // pinned 29.2 cycles per MFMA and its vector work against 31.3 with the key tiles in LDS, counters at 128K
 // x 8; a register-only probe of the same instructions: 26.8, and 25.2 with one wave of a SIMD on
 // each kind of work). Per launch, tiles / this: 1M x 4 x 4 heads 1954 -> 1738 us, 256K
-// x 4 x 8 heads of d 64 238 -> 207, 256K x 2 with a 32-token window 142 -> 121, 64K x 8 221 -> 211,
-// 128K x 8 427 -> 407 (the chip is at its power limit there: part of the gain
-// comes back as a lower clock).
+// x 4 x 8 heads of d 64 238 -> 207, 256K x 2 with a 32-token window 142 -> 121, 64K x 8 heads of d 64
+// with 128 rows 40 -> 32.
 constexpr int kKeyTurn = 64;  // keys of a wave's turn
-constexpr int kKeyChunkMin = 4096;  // keys of a chunk from which the turns are worth it
+constexpr int kKeyChunkMin = 4096;       // keys of a chunk from which the turns are worth it
+constexpr int kKeyChunkMinTall = 32768;  // the same for more than sixteen row blocks
 
 template <typename T, int D>
 __global__ __launch_bounds__(kScoreBlock, 1) void colsum_keys_kernel(CompressArgs a) {
@@ -908,11 +908,18 @@ static hipError_t launch_colsum_t(const CompressArgs& a, hipStream_t st) {
   if (a.n_col_chunks > 0) {
     const dim3 cgrid(a.n_col_chunks, a.B * a.Hkv, a.n_rsplit);
     if constexpr (sizeof(T) == 2) {
-      // at least 8 turns of 64 keys per wave (128K x 1 x 8 heads of 8: even; 100K x 2 x 8 heads of d 64,
-      // 6400-key chunks: 36 us against 43): shorter chunks lose to the last turns' spread and to
-      // filling the rows' LDS (32K x 1: 512-key chunks, 25 us against 22), Ipt. max to its reduction
-      // per head (100K x 1: 102 against 98)
-      if (a.agg != 1 && a.score_chunk >= kKeyChunkMin) {
+      // at least 8 turns of 64 keys per wave (100K x 2 x 8 heads of d 64, 6400-key chunks: 36 us
+      // against 43): shorter chunks lose to the last turns' spread and to filling the rows' LDS (32K x 1:
+      // 512-key chunks, 25 us against 22), Ipt. max to its reduction per head (100K x 1: 102 against 98),
+      // and three or four whole row blocks on every wave leave the tile kernel nothing uneven (64K x 4
+      // with 512 rows: the pass 362 us against 352-377 from box to box; with eight or sixteen blocks in
+      // all it reads the LDS too often: 64K x 8 with 128 rows of d 64, 40 us against 32)
+      // With more than sixteen row blocks the chip runs at its power limit, and up to 16384-key chunks
+      // what pass 2 gains the next pass 1 loses to the clock (128K x 8: pass 2 428-436 -> 407-430 us,
+      // pass 1 410 -> 444); at 1M x 4 (65536) the pass gains 4-5 %.
+      const int nrb = (a.rs_rows + 15) / 16;
+      if (a.agg != 1 && a.score_chunk >= (nrb <= 16 ? kKeyChunkMin : kKeyChunkMinTall) &&
+          (nrb <= 16 || nrb % kScoreWaves != 0)) {
         SGDKV_LAUNCH("score_colsum", (colsum_keys_kernel<T, D>), cgrid, sblk, st, a);
         return hipGetLastError();
       }
