@@ -473,7 +473,7 @@ __global__ __launch_bounds__(kSegBlock) void select_segment_kernel(CompressArgs 
   constexpr int WIN = CAP + 4 * NQ + 2 * kPoolHalo + 8;
   __shared__ __attribute__((aligned(16))) float win[WIN];  // column sums, then scores, then kept positions
   __shared__ __attribute__((aligned(16))) uint32_t hist[3 * kSegBins];
-  __shared__ uint32_t wa[kSegWaves], wb[kSegWaves];
+  __shared__ uint32_t wa[kSegWaves], wb[kSegWaves], wc[kSegWaves];
   __shared__ uint32_t pick[3];
   const int seg = blockIdx.x, part = blockIdx.y, parts = gridDim.y;  // parts divides kSegWaves
   const int b = seg / a.Hkv, h = seg % a.Hkv;
@@ -769,15 +769,17 @@ __global__ __launch_bounds__(kSegBlock) void select_segment_kernel(CompressArgs 
   }
   const uint32_t own = above | (eq << 16);
   const uint32_t incl = wave_scan(own);
-  if (lane == 63) wa[wid] = incl;
+  // an array of its own: with all candidates equal no barrier lies between the reads of wa and wb above
+  // and this store
+  if (lane == 63) wc[wid] = incl;
   __syncthreads();
   uint32_t before = incl - own, first = 0, last = 0;  // kept rows before the part's waves, and with them
 #pragma unroll
   for (int w = 0; w <= kSegWaves; ++w) {
     if (w == w0) first = last;
     if (w == w1 || w == kSegWaves) break;
-    before += w < wid ? wa[w] : 0u;
-    last += wa[w];
+    before += w < wid ? wc[w] : 0u;
+    last += wc[w];
   }
   uint32_t er = before >> 16;
   auto rows = [&](uint32_t c) {  // kept rows among candidates counted as c

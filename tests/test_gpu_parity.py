@@ -262,6 +262,34 @@ def test_selection_by_segment_size(n, kp, ties, fixed):
         _check_gather(res, t["k"], t["v"], budgets)
 
 
+@pytest.mark.parametrize("n,kp,fixed,one", [
+    (5, 1, (2, 34), True), (4097, 7, (2048, 2080), True), (36, 1, (0, 32), False), (1029, 7, (4, 36), False),
+    (8192, 1, (0, 32), False), (8193, 21, (16, 64), False), (32768, 7, (1024, 1024), False)])
+def test_selection_of_equal_scores(n, kp, fixed, one):
+    """All candidates with one score (zero keys; candidates a pooling radius from both ends), or a single
+    candidate: no digit tells them apart, so the lowest positions are kept, every time alike."""
+    B, w, (s, W) = 2, 32, fixed
+    C = n + w
+    wl, t = _tiny_inputs(B=B, C=C, seed=n + kp)
+    t["k"].zero_()
+    mid = C - s - W
+    assert (mid == 1) == one
+    for m in ([1, 0], [1, 1]) if one else ([mid // 3, mid - 1], [1, mid]):
+        budgets = s + W + np.array(m)
+        _announce(f"equal scores n={n} kp={kp} fixed={fixed} budgets={budgets.tolist()}")
+        first = None
+        for _ in range(8):
+            res, orc = _compress_both(t["q_win"], t["k"], t["v"], budgets, kp=kp, s=s, W=W) if first is None else (
+                sg.compress_layer(t["q_win"], t["k"], t["v"], budgets, pool_kernel=kp, b_sink=s, b_window=W), orc)
+            kept = res["kept_pos"].cpu().numpy()
+            assert np.unique(res["scores"][:, :, s:C - W].cpu().numpy()).size == 1
+            want = [np.r_[0:s + m[h], C - W:C] for _ in range(B) for h in range(2)]
+            assert np.array_equal(kept, np.concatenate(want))
+            first = res if first is None else first
+        _check_scores(first["scores"].cpu().numpy(), orc["pooled"], f"equal {n}")
+        _check_gather(first, t["k"], t["v"], budgets)
+
+
 def _qwen_small(B, C, seed_layer=0, Hq=28, Hkv=4, d=128, w=64):
     wl = workloads.WORKLOADS["qwen25_32k"]
     wl = workloads.Workload(wl.key, wl.name, 1, Hq, Hkv, d, C, w, 7, 64, 128, B, "bf16", 11, "beta")
