@@ -438,6 +438,11 @@ sgdkv_status plan_compress(const sgdkv_compress_desc* d, int64_t win0, CompressP
                                    sgdkv::kHistChunkMax);
   a.n_hist_chunks = (int)ceil_div(a.n_scored, a.hist_chunk);
   a.n_cmp_chunks = (int)ceil_div(a.C, a.hist_chunk);
+  // the most chunks any window position gives: a chunk holds at least nseg * n_scored / 1024 positions
+  // (so at most 1024 / nseg chunks, rounded up) unless that is past kHistChunkMax, and at least 1024.
+  // (Fewer scored keys than C can round to a shorter chunk and so to more of them than C gives.)
+  const int64_t hist_chunks_max = std::min<int64_t>(
+      ceil_div(a.C, 1024), std::max<int64_t>(ceil_div(a.C, sgdkv::kHistChunkMax), ceil_div(1024, nseg)));
 
   size_t off = 0;
   p.off_lse_part = off;
@@ -451,7 +456,7 @@ sgdkv_status plan_compress(const sgdkv_compress_desc* d, int64_t win0, CompressP
   p.off_hist = off;
   off += align256((size_t)nseg * 4 * 256 * sizeof(uint32_t));  // one 256-bin histogram per radix digit
   p.off_chunk_hist = off;
-  off += align256((size_t)nseg * a.n_hist_chunks * sgdkv::kChunkHistWords * sizeof(uint32_t));
+  off += align256((size_t)nseg * hist_chunks_max * sgdkv::kChunkHistWords * sizeof(uint32_t));
   p.bytes = off;
   return SGDKV_OK;
 }

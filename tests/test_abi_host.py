@@ -275,6 +275,25 @@ def test_workspace_size_independent_of_budgets():
     assert sg.compress_workspace_size(_desc(batch=2)) > n
 
 
+def test_workspace_size_covers_every_window_position():
+    """The size the library reports holds for whatever window position the call then has: lengths around
+    the ones where a pooling workgroup's positions grow by 256 (2^18 k scored keys over the batch), with
+    the window at the end, before a question, early in the prompt and after it."""
+    if _gpu():
+        pytest.skip("well-formed calls end at the missing device")
+    for B, Hkv in ((1, 4), (8, 4), (3, 2), (2, 8), (1, 1), (40, 8)):
+        for k in (1, 4, 5, 8, 13, 31, 32, 33):
+            for j in (-70, -1, 0, 1, 40, 63, 64, 65, 300):
+                C = (k << 18) // (B * Hkv) + j
+                for back in (64, 264, C // 2, C - 1, 0):
+                    if C < 64 or back > C:
+                        continue
+                    desc = _desc(batch=B, num_q_heads=7 * Hkv, num_kv_heads=Hkv, head_dim=128, obs_window=64,
+                                 seq_len=C, b_sink=0, b_window=max(back, 1), dtype=sg.DTYPE_BF16)
+                    got = _compress_ex(desc, sg.GROUP_MEAN, None, (C,) * Hkv, window_pos=C - back)
+                    assert got == sg.ERR_HIP, (B, Hkv, C, back, sg.load_library().sgdkv_last_error())
+
+
 def test_window_rows_beyond_one_workgroup():
     """G*w up to 4096 window rows per KV head: the rows are split over several score workgroups,
     each leaving its own column-sum partial, so the workspace grows with the number of splits."""
