@@ -783,11 +783,12 @@ sgdkv_status plan_decode(const sgdkv_decode_desc* d, const int64_t* offsets_host
   if ((int64_t)d->batch * d->num_q_heads > 0x7FFFFFFFll) return fail(SGDKV_ERR_UNSUPPORTED, "batch * num_q_heads");
   const int64_t rb = (int64_t)d->head_dim * (d->kv_dtype == 1 ? 2 : 4);
   if (offsets_host[0] < 0) return fail(SGDKV_ERR_INVALID_ARG, "offsets[0] < 0");
-  int64_t longest = 0;
+  int64_t longest = 0, filled = 0;  // filled: segments with rows
   for (int64_t i = 0; i < nseg; ++i) {
     const int64_t len = offsets_host[i + 1] - offsets_host[i];
     if (len < 0) return fail(SGDKV_ERR_INVALID_ARG, "offsets decrease at %lld", (long long)i);
     longest = std::max(longest, len);
+    filled += len > 0;
   }
   if (longest * rb > 0xFFFFFFFFll) return fail(SGDKV_ERR_UNSUPPORTED, "a segment exceeds 4 GiB");
   const int64_t total = offsets_host[nseg];
@@ -809,26 +810,41 @@ sgdkv_status plan_decode(const sgdkv_decode_desc* d, const int64_t* offsets_host
   a.chunk = std::min<int64_t>(
       std::max<int64_t>(round_up(ceil_div(total - offsets_host[0], kDecodeSplits), 64), kDecodeMinChunk), 1 << 24);
   // A cache small enough gets the shortest splits (of at least 64 rows) that launch at most one
-  // workgroup per compute unit, with room for one of appended rows per segment (up to 32; whatever the
-  // capacity, so that a call without appended rows does not depend on it): two workgroups on one unit take nearly twice as long as one, and 64-row splits at any
-  // count (or 128-row ones past 256 workgroups) left units with two beside units with one. Decode per
-  // call, so chosen / as before: 143K rows 20.6 / 28.2 us, 168K 24.9 / 31.4, 106K 19.3 / 23.7, 264K 31.0 / 35.5,
-  // 318K 33.0 / 36.3. Past 320 rows a split two rounds of shorter ones are as fast (287K rows: 288
-  // rows 35.4, 320 31.3, two rounds 33.9). Below 64 rows the partials to combine cost more than
-  // the shorter splits save (39K rows: 48 rows 15.0, 64 14.5).
+  // workgroup per compute unit, with room for one of appended rows per segment (up to 32; whatever
+  // the capacity, so that a call without appended rows does not depend on it): two workgroups on one
+  // unit take nearly twice as long as one, and 64-row splits at any count (or 128-row ones past 256
+  // workgroups) left units with two beside units with one. Decode per call, so chosen / as before:
+  // 143K rows 20.6 / 28.2 us, 168K 24.9 / 31.4, 106K 19.3 / 23.7, 264K 31.0 / 35.5, 318K 33.0 / 36.3.
+  // Past 320 rows a split two rounds of shorter ones are as fast (287K rows: 288 rows 35.4, 320
+  // 31.3, two rounds 33.9). Below 64 rows the partials to combine cost more than the shorter splits
+  // save (39K rows: 48 rows 15.0, 64 14.5). A filled segment takes a workgroup at any split length, so
+  // more of those than units leave nothing to look for (256 segments of 150 rows: 4 us of host time
+  // per plan, 18 with every length tried).
   // One that would launch more than two rounds gets splits twice as long (fewer workgroups, each with
   // less of its fixed cost per row, and fewer partials to combine: decode per 128K x B 8 layer -3.7 %;
   // the 256K x B 16 and 1M x B 32 caches already have splits of 512 rows and more)
   const int wpw = sgdkv::kDecodeWaves;  // splits (waves) per decode workgroup
   if (a.chunk == kDecodeMinChunk) {
-    auto workgroups = [&](int64_t chunk) {
+    auto workgroups = [&](int64_t chunk) {  // never more for longer splits
+      const uint32_t rows = (uint32_t)(chunk * wpw);
       int64_t n = 0;
-      for (int64_t i = 0; i < nseg; ++i) n += ceil_div(ceil_div(offsets_host[i + 1] - offsets_host[i], chunk), wpw);
+      for (int64_t i = 0; i < nseg; ++i)  // a segment's rows fit 32 bits with room (it holds at most 4 GiB)
+        n += ((uint32_t)(offsets_host[i + 1] - offsets_host[i]) + rows - 1) / rows;
       return n;
     };
     const int64_t units = sgdkv::kScoreWorkgroups - std::min<int64_t>(nseg, sgdkv::kScoreWorkgroups / 8);
+    // c: the shortest length in steps of 16 rows that fits, past kDecodeUnitChunk if none does
     int64_t c = std::max<int64_t>(round_up(ceil_div(total - offsets_host[0], units * wpw), 16), kDecodeMinChunk / 2);
-    while (c <= kDecodeUnitChunk && workgroups(c) > units) c += 16;
+    if (filled > units || (c <= kDecodeUnitChunk && workgroups(kDecodeUnitChunk) > units)) {
+      c = kDecodeUnitChunk + 16;
+    } else if (c < kDecodeUnitChunk && workgroups(c) > units) {
+      int64_t fits = kDecodeUnitChunk;  // c does not
+      while (fits - c > 16) {
+        const int64_t mid = c + (fits - c) / 32 * 16;
+        (workgroups(mid) > units ? c : fits) = mid;
+      }
+      c = fits;
+    }
     if (c <= kDecodeUnitChunk) a.chunk = c;
     else if (workgroups(a.chunk) > 2 * kDecodeResident) a.chunk = kDecodeMinChunk * 2;
   }

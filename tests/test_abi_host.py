@@ -10,6 +10,7 @@
 import ctypes
 import os
 import re
+import time
 
 import numpy as np
 import pytest
@@ -471,6 +472,45 @@ def test_decode_workgroups_fill_whole_rounds():
     desc = sg.DecodeDesc(1, 4 * G, 4, d, sg.DTYPE_BF16, sg.DTYPE_F32, 0.0)
     oh = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
     assert sg.decode_workspace_size(desc, oh) // per_wg == 2 + 0 + 4 + 1
+
+
+def test_decode_planning_time_of_many_short_segments():
+    """More filled segments than compute units leave the plan no split length to look for: planning 20000
+    segments of two rows takes a few passes over the offsets, as planning 20000 empty ones does (with
+    every split length tried: seven times as long)."""
+    lib = sg.load_library()
+    desc = sg.DecodeDesc(2500, 64, 8, 128, sg.DTYPE_BF16, sg.DTYPE_F32, 0.0)
+    need = ctypes.c_size_t(0)
+
+    def best(rows):
+        oh = np.arange(20001, dtype=np.int64) * rows
+        times = []
+        for _ in range(40):
+            t0 = time.perf_counter()
+            assert lib.sgdkv_decode_workspace_size(ctypes.byref(desc), sg._np_ptr(oh), ctypes.byref(need)) == sg.OK
+            times.append(time.perf_counter() - t0)
+        return min(times)
+
+    assert best(2) < 3 * best(0)
+
+
+@pytest.mark.parametrize("lens", [[143000 // 32] * 32, [20000, 0, 17, 60000], [1] * 224, [1] * 225, [1279] * 224,
+                                  [1281] * 224, [3000, 40] * 40, [0, 300000], [286720 // 4] * 4, [64] * 512])
+@pytest.mark.parametrize("cap", [0, 300])
+def test_decode_split_length_of_small_caches(lens, cap):
+    """The plan takes the shortest splits of 64 to 320 rows, in steps of 16, that launch at most a
+    workgroup (four splits) per compute unit less room for a segment's appended rows; if none does, 128
+    rows, or 256 where those launch more than two rounds."""
+    G, d, n = 7, 128, len(lens)
+    desc = sg.DecodeDesc(1, n * G, n, d, sg.DTYPE_BF16, sg.DTYPE_F32, 0.0)
+    oh = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+    wgs = lambda c: int(sum(-(-l // (4 * c)) for l in lens))
+    units = 256 - min(n, 32)
+    fits = [c for c in range(64, 321, 16) if wgs(c) <= units]
+    chunk = fits[0] if fits else 256 if wgs(128) > 1024 else 128
+    if wgs(chunk) <= 512:  # past one round the workgroups are shared out over whole rounds
+        slots = wgs(chunk) + n * -(-cap // (4 * chunk))
+        assert sg.decode_workspace_size(desc, oh, cap) == -(-slots * G * (d + 2) * 4 // 256) * 256
 
 
 def test_decode_workspace_with_appended_rows():
