@@ -153,10 +153,11 @@ KERNEL_OF = {  # demangled ("sgdkv::name<...") or mangled ("_ZN5sgdkv<len>name..
     "pool_radix_hist": r"sgdkv(::|\d+)radix_pass_kernel(<0, true, true|ILi0ELb1ELb1E)",
     "radix_hist": r"sgdkv(::|\d+)radix_pass_kernel(<[123], false, true|ILi[123]ELb0ELb1E)",
     "compact": r"sgdkv(::|\d+)compact_kernel"}
-SOURCE_OF = {"score_lse": "score_kernels.hip", "score_colsum": "score_kernels.hip", "lse_merge": "score_kernels.hip",
-             "gather": "select_kernels.hip", "pool_radix_hist": "select_kernels.hip", "radix_hist": "select_kernels.hip",
-             "compact": "select_kernels.hip",
-             "decode_split": "decode_kernels.hip", "decode_combine": "decode_kernels.hip"}
+SCORE_SOURCES = ("lse_pass.h", "lse_kernels.hip", "lse_kernels_ilp.hip", "score_kernels.hip", "score_common.h")
+SOURCE_OF = {"score_lse": SCORE_SOURCES, "score_colsum": SCORE_SOURCES, "lse_merge": SCORE_SOURCES,
+             "gather": ("select_kernels.hip",), "pool_radix_hist": ("select_kernels.hip",),
+             "radix_hist": ("select_kernels.hip",), "compact": ("select_kernels.hip",),
+             "decode_split": ("decode_kernels.hip",), "decode_combine": ("decode_kernels.hip",)}
 SHARED_SOURCES = ("device_common.h", "mfma_frag.h", "sgdkv_internal.h", "segment_init.h")
 
 
@@ -166,7 +167,7 @@ def source_sha(name):
     import hashlib
     import re
     h = hashlib.sha256()
-    for f in (SOURCE_OF[name],) + SHARED_SOURCES:
+    for f in SOURCE_OF[name] + SHARED_SOURCES:
         with open(os.path.join(ROOT, "paper_2609_03235_amd", "csrc", f)) as fh:
             text = fh.read()
         text = re.sub(r"/\*.*?\*/", " ", text, flags=re.S)

@@ -8,7 +8,7 @@
 // the G*w rows of its query group are one dense block R x d, so the logits of
 // a key tile are an R x 16 MFMA product.
 //
-//   pass 1 (lse_kernel + lse_merge_kernel): base-2 log-sum-exp of every
+//   pass 1 (lse_kernel + lse_merge_kernel, lse_pass.h): base-2 log-sum-exp of every
 //     window row over its causal keys. Each workgroup covers one chunk of
 //     keys (about one workgroup per CU per launch) and leaves per-row partials
 //     (m, s); the merge combines the chunks in a fixed order, in fp64.
@@ -22,7 +22,7 @@
 // v+4) covers a quarter of the rows. A workgroup holds at most 512 rows; a
 // KV head with more window rows (G*w > 512, e.g. the 128-token window of the
 // paper's main setting with GQA groups of 7 or 8) splits them over several
-// workgroups per key chunk (grid z = row split). Pass 1 partials are per row
+// workgroups per key chunk (pass 2: grid z; pass 1: grid x, with the segments). Pass 1 partials are per row
 // anyway; pass 2 then leaves one column-sum partial per split, which the
 // pooling pass adds (or, for Ipt. max, maximises) in split order. Each key tile (128 keys; 64 in pass 2
 // for fp32 keys) is staged once in LDS and read by all eight waves as B-fragments;
@@ -30,460 +30,10 @@
 // f32 for fp32 inputs) accumulates in fp32.
 // Output layout of a 16x16 MFMA: lane l holds rows 4*(l/16)+0..3 of key
 // column l%16.
-#include "device_common.h"
-#include "mfma_frag.h"
-#include "sgdkv_internal.h"
+#include "score_common.h"
 #include "segment_init.h"
 
-// Row blocks per wave the dispatch instantiates: at most 512 rows (one row split) over all waves.
-#define SGDKV_SCORE_WAVES_MAX_RBW (kMaxSplitRowsMacro / (16 * SGDKV_SCORE_WAVES))
-#define kMaxSplitRowsMacro 512
-
 namespace sgdkv {
-
-// Shared pieces of both passes ------------------------------------------------
-template <typename T>
-constexpr int col_tile() {
-  return sizeof(T) == 2 ? kColTileBf16 : kColTileF32;
-}
-
-template <typename T, int D>
-struct TileGeom {
-  static constexpr int EB = elt_bytes<T>();
-  static constexpr int RB = D * EB;           // bytes per key row
-  static constexpr int LDS_STRIDE = RB + 32;  // padded row pitch: 16-B fragment reads free of bank conflicts (measured)
-  static constexpr int NC = D / 32;           // 32-wide k chunks
-  static constexpr int V16 = RB / 16;         // 16-byte vectors per row
-};
-
-// K tile staging: keys [tile0, tile0+TILE) of this head travel global -> registers
-// (issued one tile ahead) -> LDS. Keys past the end of the head read as zeros.
-template <typename T, int D, int TILE>
-struct KeyStage {
-  using G = TileGeom<T, D>;
-  static constexpr int TOT = TILE * G::V16;                        // 16-byte vectors per tile
-  static constexpr int N = (TOT + kScoreBlock - 1) / kScoreBlock;  // per thread
-  static constexpr bool ALL = TOT >= kScoreBlock;                  // every thread moves N vectors
-  static_assert(TOT % kScoreBlock == 0 || !ALL, "tile must split evenly");
-  u32x4 r[N];
-  __device__ __forceinline__ void load(rsrc_t kr, int64_t tile0) {
-    if (ALL || (int)threadIdx.x < TOT) {
-#pragma unroll
-      for (int u = 0; u < N; ++u) {
-        const int vi = threadIdx.x + u * kScoreBlock;
-        const int row = vi / G::V16, c16 = vi % G::V16;
-        r[u] = ld128(kr, (uint32_t)((tile0 + row) * G::RB + c16 * 16));
-      }
-    }
-  }
-  __device__ __forceinline__ void store(char* ktile) const {
-    if (ALL || (int)threadIdx.x < TOT) {
-#pragma unroll
-      for (int u = 0; u < N; ++u) {
-        const int vi = threadIdx.x + u * kScoreBlock;
-        const int row = vi / G::V16, c16 = vi % G::V16;
-        *reinterpret_cast<u32x4*>(ktile + row * G::LDS_STRIDE + c16 * 16) = r[u];
-      }
-    }
-  }
-};
-
-// Row block of slot j of wave wid: blocks wid, wid+8, ... (interleaved), or, with HW (head
-// waves), blocks wid*RBW .. wid*RBW+RBW-1, so that the rows of a wave belong to one query head
-// when w is a multiple of 16*RBW. Balanced head waves (bal: seven heads of one wave each, the
-// group size of a 28/4-head model): the last wave, which would hold no rows, takes the last
-// block of the heads of waves 4-6 (slots 0-2), so that each SIMD (waves s and s+4) carries
-// 2*RBW - 1 blocks instead of 2*RBW on three SIMDs and RBW on the fourth.
-constexpr int kBalFirstWave = kScoreWaves / 2;  // heads of waves 4-6 lend their last block
-template <int RBW, bool HW>
-__device__ __forceinline__ int row_block(int wid, int j, bool bal = false) {
-  if (HW && bal && wid == kScoreWaves - 1) return (kBalFirstWave + j) * RBW + RBW - 1;
-  return HW ? wid * RBW + j : wid + kScoreWaves * j;
-}
-
-// Window rows [r0, r0 + nrows) of KV head h (one row split) as A fragments.
-template <typename T, int D, int RBW, bool HW = false>
-__device__ __forceinline__ void load_group_queries(const CompressArgs& a, int b, int h, int r0, int nrows, int wid,
-                                                   int lane, Frag<T> (&qa)[RBW][D / 32], bool bal = false) {
-  using G = TileGeom<T, D>;
-  const T* qbase = static_cast<const T*>(a.q_win) + ((int64_t)(b * a.Hq + h * a.G) * a.w + r0) * D;
-  const rsrc_t qr = make_rsrc(qbase, (uint64_t)nrows * G::RB);
-  const int lr = lane & 15, lg = lane >> 4;
-#pragma unroll
-  for (int j = 0; j < RBW; ++j) {
-    const int row = row_block<RBW, HW>(wid, j, bal) * 16 + lr;  // rows >= nrows read as zeros
-#pragma unroll
-    for (int c = 0; c < G::NC; ++c)
-      qa[j][c] = gload_frag<T>(qr, (uint32_t)(row * G::RB + (32 * c + 8 * lg) * G::EB));
-  }
-}
-
-// Chunk pipeline --------------------------------------------------------------
-//
-// A workgroup streams the key tiles of its chunk through two LDS buffers and
-// the MFMAs as one rolling pipeline. In step s of tile t a wave issues the
-// MFMAs of the next subtile (16 keys), reads the key fragments of the subtile
-// after that from LDS, and hands the logits of subtile s to the vector ALU.
-// Tile t+1 goes into the other buffer at the start of tile t (its global loads
-// were issued one tile earlier), and the tile's single barrier, two subtiles
-// before its end, makes that buffer readable; the buffer written at the start
-// of tile t was last read before the barrier of tile t-1. The MFMAs of the
-// subtile after the chunk's last one run on whatever keys follow (zeros past
-// the head) and are discarded. REV streams the chunk's tiles last to first
-// (step t covers tile ntiles-1-t; the steps after the last read zeros). On
-// gfx950 a wave's own MFMAs and vector instructions issue one after the other,
-// and exp2 overlaps little with the MFMAs of the SIMD's other wave; the two
-// waves of a SIMD mainly hide each other's latencies.
-template <typename T, int D, int NB>
-__device__ __forceinline__ void subtile_mfma(const Frag<T> (&qa)[NB > 0 ? NB : 1][D / 32],
-                                             const Frag<T> (&kb)[D / 32], f32x4 (&acc)[NB > 0 ? NB : 1]) {
-#pragma unroll
-  for (int c = 0; c < D / 32; ++c)
-#pragma unroll
-    for (int j = 0; j < NB; ++j) acc[j] = mma(qa[j][c], kb[c], c == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : acc[j]);
-}
-
-// One step of the pipeline: the MFMAs of the next subtile and, between them, the vector work on the
-// logits of the current one, each logit's fma, exp2 and use one MFMA apart so that none waits for
-// the one before it.
-template <typename T, int D, int NB, typename Arg, typename Use>
-__device__ __forceinline__ void subtile_step(const Frag<T> (&qa)[NB > 0 ? NB : 1][D / 32], const Frag<T> (&kb)[D / 32],
-                                             f32x4 (&nxt)[NB > 0 ? NB : 1], const f32x4 (&cur)[NB > 0 ? NB : 1],
-                                             Arg&& arg, Use&& use) {
-  constexpr int N = 4 * NB, NM = D / 32 * NB, N1 = N > 0 ? N : 1;
-  float f[N1], e[N1];
-#pragma unroll
-  for (int k = 0; k < N + 2; ++k) {
-#pragma unroll
-    for (int q = 0; q < NM; ++q)
-      if (q >= k * NM / N1 && q < (k + 1) * NM / N1) {
-        const int c = q / (NB > 0 ? NB : 1), j = q % (NB > 0 ? NB : 1);
-        nxt[j] = mma(qa[j][c], kb[c], c == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : nxt[j]);
-      }
-    if (k < N) f[k] = arg(k / 4, k % 4, cur[k / 4][k % 4]);
-    if (k >= 1 && k - 1 < N) e[k - 1] = fast_exp2(f[k - 1]);
-    if (k >= 2) use((k - 2) / 4, (k - 2) % 4, e[k - 2]);
-  }
-}
-
-template <typename T, int D>
-__device__ __forceinline__ void subtile_frags(const char* ktile, int t, int lr, int lg, Frag<T> (&kb)[D / 32]) {
-  using G = TileGeom<T, D>;
-#pragma unroll
-  for (int c = 0; c < G::NC; ++c)
-    kb[c] = lds_frag<T>(ktile, (uint32_t)((16 * t + lr) * G::LDS_STRIDE + (32 * c + 8 * lg) * G::EB));
-}
-
-// Hooks: begin(acc) once with the logits of the chunk's first subtile (before
-// any sub call); sub(t, s, acc) per subtile; at_barrier(t) right after tile t's
-// barrier. SKEW: sub(t, s, acc, nxt, kb) issues the next subtile's MFMAs itself,
-// between its vector work.
-template <typename T, int D, int NB, int TILE, bool REV, bool SKEW, typename Begin, typename Sub, typename AtBarrier>
-__device__ __forceinline__ void chunk_pipeline(char* kbuf, const rsrc_t& kr, int64_t key0, int64_t C, int64_t ntiles,
-                                               int lr, int lg, const Frag<T> (&qa)[NB > 0 ? NB : 1][D / 32],
-                                               Begin&& begin, Sub&& sub, AtBarrier&& at_barrier) {
-  using G = TileGeom<T, D>;
-  constexpr int NBX = NB > 0 ? NB : 1;
-  constexpr int S = TILE / 16;
-  constexpr int BUF = TILE * G::LDS_STRIDE;
-  static_assert(S >= 4 && S % 2 == 0, "tile geometry");
-  // keys past the head read as zeros; the clamp keeps byte offsets below 4 GiB
-  auto tile_key = [&](int64_t t) {
-    const int64_t k = REV ? (t < ntiles ? key0 + (ntiles - 1 - t) * TILE : C) : key0 + t * TILE;
-    return k < C ? k : C;
-  };
-  KeyStage<T, D, TILE> stage;
-  stage.load(kr, tile_key(0));
-  stage.store(kbuf);
-  stage.load(kr, tile_key(1));
-  __syncthreads();
-  Frag<T> kb[2][D / 32];
-  f32x4 acc[2][NBX];
-  subtile_frags<T, D>(kbuf, 0, lr, lg, kb[0]);
-  subtile_frags<T, D>(kbuf, 1, lr, lg, kb[1]);
-  subtile_mfma<T, D, NB>(qa, kb[0], acc[0]);
-  begin(acc[0]);
-  for (int64_t t = 0; t < ntiles; ++t) {
-    const char* buf = kbuf + (t & 1) * BUF;
-    char* nbuf = kbuf + ((t + 1) & 1) * BUF;
-#pragma unroll
-    for (int s = 0; s < S; ++s) {
-      if (s == 0) {
-        stage.store(nbuf);
-        stage.load(kr, tile_key(t + 2));
-      }
-      if (s == S - 2) {
-        __syncthreads();
-        at_barrier(t);
-      }
-      if constexpr (!SKEW) subtile_mfma<T, D, NB>(qa, kb[(s + 1) & 1], acc[(s + 1) & 1]);
-      if (s + 2 < S)
-        subtile_frags<T, D>(buf, s + 2, lr, lg, kb[s & 1]);
-      else
-        subtile_frags<T, D>(nbuf, s + 2 - S, lr, lg, kb[s & 1]);
-      if constexpr (SKEW)
-        sub(t, s, acc[s & 1], acc[(s + 1) & 1], kb[(s + 1) & 1]);
-      else
-        sub(t, s, acc[s & 1]);
-    }
-  }
-}
-
-// Pass 1: per-chunk partial log-sum-exp of every window row -------------------
-//
-// Each lane keeps, for each of its 4*NB row slots, a reference m and a sum
-// s = sum 2^(y - m) over the keys it has seen (y = logit * log2 e). The tiles
-// of the chunk that every window row sees in full run through the pipeline
-// with m fixed at the row's largest logit among the chunk's first 16 keys, so
-// each logit costs one fma, one exp2 and one add and the loop has no branch.
-// A sum can only overflow if a later logit exceeds that maximum by about 100
-// (base 2); the chunk's sums are checked once at its end and, if any left
-// [0, 2^122] (inf and NaN included), the whole chunk is recomputed with the
-// exact online update (two exp2 per logit, m = running max), reading the keys
-// from global memory. The bound leaves room for the 16 lanes of a row, which
-// share the reference and are then added as they are: 16 * 2^122 = 2^126 stays
-// finite. The keys that reach the window block (causal mask) or the end of the
-// head, and those before them that fill no whole tile, are tail chunks of their
-// own (lse_tail). Padded rows (past R) keep m = 0.
-template <typename T, int D, int NB, int TILE>
-__device__ __forceinline__ void lse_exact_tile(const rsrc_t& kr, int lr, int lg, int64_t tile0,
-                                               const Frag<T> (&qa)[NB > 0 ? NB : 1][D / 32], float c2,
-                                               float (&m)[NB > 0 ? NB : 1][4], float (&s)[NB > 0 ? NB : 1][4]) {
-  using G = TileGeom<T, D>;
-  constexpr int NBX = NB > 0 ? NB : 1;
-  auto load = [&](int t, Frag<T>(&kb)[D / 32]) {
-#pragma unroll
-    for (int c = 0; c < G::NC; ++c)
-      kb[c] = gload_frag<T>(kr, (uint32_t)((tile0 + 16 * t + lr) * G::RB + (32 * c + 8 * lg) * G::EB));
-  };
-  Frag<T> kn[D / 32];
-  load(0, kn);
-#pragma unroll 1
-  for (int t = 0; t < TILE / 16; ++t) {
-    Frag<T> kb[D / 32];
-#pragma unroll
-    for (int c = 0; c < G::NC; ++c) kb[c] = kn[c];
-    load(t + 1 < TILE / 16 ? t + 1 : t, kn);  // the next subtile's keys are in flight during this one
-    f32x4 acc[NBX];
-    subtile_mfma<T, D, NB>(qa, kb, acc);
-#pragma unroll
-    for (int j = 0; j < NB; ++j)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const float y = acc[j][i] * c2;
-        const float mn = fmaxf(m[j][i], y);
-        if (mn != -INFINITY) {
-          s[j][i] = s[j][i] * fast_exp2(m[j][i] - mn) + fast_exp2(y - mn);
-          m[j][i] = mn;
-        }
-      }
-  }
-}
-
-// Combines the 16 lanes (keys) of each row and stores the row's (m, s) of this chunk.
-template <int NB>
-__device__ __forceinline__ void lse_store(const CompressArgs& a, int seg, int chunk, int r0, int nrows, int wid,
-                                          int lane, const float (&m)[NB > 0 ? NB : 1][4],
-                                          const float (&s)[NB > 0 ? NB : 1][4]) {
-  const int lr = lane & 15, lg = lane >> 4;
-  float* part = a.lse_part + ((int64_t)seg * a.n_lse_chunks + chunk) * a.R * 2;
-  const rsrc_t pr = make_rsrc(part, (uint64_t)a.R * 2 * sizeof(float));
-#pragma unroll
-  for (int j = 0; j < NB; ++j)
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const float mx = row16_max(m[j][i]);
-      const float ss = row16_sum(m[j][i] == -INFINITY ? 0.f : s[j][i] * fast_exp2(m[j][i] - mx));
-      const int row = (wid + kScoreWaves * j) * 16 + 4 * lg + i;
-      if (lr == 0 && row < nrows)
-        st64(pr, (uint32_t)((r0 + row) * 8), (uint64_t)__float_as_uint(mx) | ((uint64_t)__float_as_uint(ss) << 32));
-    }
-}
-
-// The keys of a tail chunk (at most kLseTail, from the last whole tile every window row sees to the
-// last key some row sees): all products at once, the causal mask, then one exp2 per logit against
-// the lane's own maximum. No LDS and no loop; a workgroup is bound by the latency of its queries'
-// and keys' loads. (One workgroup per segment walking all of them 16 keys at a time, each load
-// waiting for the one before, ended the launch on short prompts: pass 1 at 6K x 1 24 us, now 14.6,
-// at 2K fp32 12 us, now 9; event pairs around the launches included.)
-template <typename T, int D, int NB>
-__device__ __forceinline__ void lse_tail(const CompressArgs& a, int seg, int chunk, int r0, int nrows, int wid, int lane,
-                                         const Frag<T> (&qa)[NB > 0 ? NB : 1][D / 32], const rsrc_t& kr) {
-  using G = TileGeom<T, D>;
-  constexpr int NBX = NB > 0 ? NB : 1, S = kLseTail / 16;
-  const int64_t key0 = a.lse_tail0 + (int64_t)(chunk - a.n_lse_head) * kLseTail;
-  const int lr = lane & 15, lg = lane >> 4;
-  Frag<T> kb[S][G::NC];
-#pragma unroll
-  for (int t = 0; t < S; ++t)
-#pragma unroll
-    for (int c = 0; c < G::NC; ++c)
-      kb[t][c] = gload_frag<T>(kr, (uint32_t)((key0 + 16 * t + lr) * G::RB + (32 * c + 8 * lg) * G::EB));
-  f32x4 acc[S][NBX];
-#pragma unroll
-  for (int t = 0; t < S; ++t) subtile_mfma<T, D, NB>(qa, kb[t], acc[t]);
-  int dk[S];  // key - window position; keys past the head are never visible
-#pragma unroll
-  for (int t = 0; t < S; ++t) {
-    const int64_t key = key0 + 16 * t + lr;
-    dk[t] = key < a.C ? (int)(key - a.win0) : 1 << 30;  // tail keys lie within 2^16 of the window
-  }
-  float m[NBX][4], s[NBX][4];
-  int wj = (r0 + wid * 16 + 4 * lg) % a.w;  // window index of the lane's first row
-  const int step = (kScoreWaves * 16) % a.w;
-#pragma unroll
-  for (int j = 0; j < NB; ++j) {
-    int wi = wj;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      float y[S], mx = -INFINITY;
-#pragma unroll
-      for (int t = 0; t < S; ++t) {
-        y[t] = dk[t] > wi ? -INFINITY : acc[t][j][i] * a.c2;
-        mx = fmaxf(mx, y[t]);
-      }
-      m[j][i] = mx;
-      s[j][i] = 0.f;
-#pragma unroll
-      for (int t = 0; t < S; ++t) s[j][i] += fast_exp2(y[t] - (mx == -INFINITY ? 0.f : mx));
-      wi = wi + 1 == a.w ? 0 : wi + 1;
-    }
-    wj = wj + step >= a.w ? wj + step - a.w : wj + step;
-  }
-  lse_store<NB>(a, seg, chunk, r0, nrows, wid, lane, m, s);
-}
-
-template <typename T, int D, int NB>
-__device__ void lse_chunk(const CompressArgs& a, char* kbuf, int seg, int chunk, int r0, int nrows, int wid,
-                          int lane, const Frag<T> (&qa)[NB > 0 ? NB : 1][D / 32], const rsrc_t& kr, int64_t key0,
-                          int64_t key_end) {
-  constexpr int NBX = NB > 0 ? NB : 1;
-  constexpr int TILE = kLseTile;
-  const int lr = lane & 15, lg = lane >> 4;
-  const float c2 = a.c2;
-  float m[NBX][4], s[NBX][4];
-  bool real[NBX][4];
-  auto reset = [&]() {
-#pragma unroll
-    for (int j = 0; j < NBX; ++j)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        m[j][i] = real[j][i] ? -INFINITY : 0.f;  // a padded row must not force the exact path
-        s[j][i] = 0.f;
-      }
-  };
-#pragma unroll
-  for (int j = 0; j < NBX; ++j)
-#pragma unroll
-    for (int i = 0; i < 4; ++i) real[j][i] = (wid + kScoreWaves * j) * 16 + 4 * lg + i < nrows;
-  reset();
-  const int64_t nfast = (key_end - key0) / TILE;  // whole tiles every row sees (>= 1)
-  {
-    chunk_pipeline<T, D, NB, TILE, false, true>(
-        kbuf, kr, key0, a.C, nfast, lr, lg, qa,
-        [&](const f32x4(&acc)[NBX]) {
-#pragma unroll
-          for (int j = 0; j < NB; ++j)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-              const float mx = row16_max(acc[j][i] * c2);  // every lane of the 16-lane row takes part
-              if (real[j][i]) m[j][i] = mx;
-            }
-        },
-        [&](int64_t, int, const f32x4(&acc)[NBX], f32x4(&nxt)[NBX], const Frag<T>(&kb)[D / 32]) {
-          subtile_step<T, D, NB>(qa, kb, nxt, acc, [&](int j, int i, float x) { return fmaf(x, c2, -m[j][i]); },
-                                 [&](int j, int i, float e) { s[j][i] += e; });
-        },
-        [&](int64_t) {});
-    bool bad = false;
-#pragma unroll
-    for (int j = 0; j < NB; ++j)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) bad |= !(s[j][i] <= 5.3169119831396635e36f);  // 2^122; catches inf and NaN
-    if (__any(bad)) {
-      reset();
-      for (int64_t t = 0; t < nfast; ++t)
-        lse_exact_tile<T, D, NB, TILE>(kr, lr, lg, key0 + t * TILE, qa, c2, m, s);
-    }
-  }
-  lse_store<NB>(a, seg, chunk, r0, nrows, wid, lane, m, s);
-}
-
-template <typename T, int D, int RBW>
-__global__ __launch_bounds__(kScoreBlock, 1) void lse_kernel(CompressArgs a) {
-  using G = TileGeom<T, D>;
-  __shared__ __attribute__((aligned(16))) char ktile[2 * kLseTile * G::LDS_STRIDE];
-  const int nseg = a.B * a.Hkv;
-  const int seg = (int)blockIdx.x % nseg, split = (int)blockIdx.x / nseg;
-  const int b = seg / a.Hkv, h = seg % a.Hkv;
-  // The uniform chunks of keys every row sees come first in the grid, then the short tail chunks, if
-  // those have workgroups of their own (with both mixed segment by segment, some shader engines got
-  // more long workgroups than they have compute units: 766 us for 420 at 128K x 8); otherwise the
-  // last uniform chunk's workgroup goes on to them. Keys past the last window row's position are
-  // seen by no row.
-  const int chunk = (int)blockIdx.y;
-  const int64_t key0 = (int64_t)chunk * a.lse_chunk;
-  const int64_t key_end = key0 + a.lse_chunk < a.lse_tail0 ? key0 + a.lse_chunk : a.lse_tail0;
-  const int tail0 = chunk >= a.n_lse_head ? chunk : a.n_lse_head;  // tail chunks of this workgroup
-  const int tail1 = chunk >= a.n_lse_head ? chunk + 1
-                    : chunk == a.n_lse_head - 1 && (int)gridDim.y == a.n_lse_head ? a.n_lse_chunks : 0;
-  const int tid = threadIdx.x, wid = tid >> 6, lane = tid & 63;
-  const int r0 = split * a.lse_rs_rows;
-  const int nrows = a.R - r0 < a.lse_rs_rows ? a.R - r0 : a.lse_rs_rows;
-  const rsrc_t kr = make_rsrc(static_cast<const T*>(a.k) + (int64_t)seg * a.C * D, (uint64_t)a.C * G::RB);
-  Frag<T> qa[RBW][G::NC];
-  load_group_queries<T, D, RBW>(a, b, h, r0, nrows, wid, lane, qa);
-  // blocks this wave owns: RBW or RBW-1 (uniform per wave)
-  const int nrb = (nrows + 15) / 16;
-  if (wid + kScoreWaves * (RBW - 1) < nrb) {
-    if (chunk < a.n_lse_head)
-      lse_chunk<T, D, RBW>(a, ktile, seg, chunk, r0, nrows, wid, lane, qa, kr, key0, key_end);
-    for (int c = tail0; c < tail1; ++c) lse_tail<T, D, RBW>(a, seg, c, r0, nrows, wid, lane, qa, kr);
-  } else {
-    Frag<T> qb[RBW > 1 ? RBW - 1 : 1][G::NC];
-#pragma unroll
-    for (int j = 0; j < RBW - 1; ++j)
-#pragma unroll
-      for (int c = 0; c < G::NC; ++c) qb[j][c] = qa[j][c];
-    if (chunk < a.n_lse_head)
-      lse_chunk<T, D, RBW - 1>(a, ktile, seg, chunk, r0, nrows, wid, lane, qb, kr, key0, key_end);
-    for (int c = tail0; c < tail1; ++c) lse_tail<T, D, RBW - 1>(a, seg, c, r0, nrows, wid, lane, qb, kr);
-  }
-}
-
-// Merge the per-chunk partials of every window row in fp64: 16 lanes per row (16 rows per
-// workgroup of segment blockIdx.y), lane l taking chunks l, l+16, ...; the maximum of the chunk
-// references over the 16 lanes, then each lane's rescaled sums in chunk order, and the 16 lane
-// sums added in a fixed butterfly order. A row's lanes read neighbouring chunks' partials.
-constexpr int kMergeLanes = 16;
-__global__ __launch_bounds__(kBlock) void lse_merge_kernel(CompressArgs a) {
-  const int64_t seg = blockIdx.y;
-  const int lane = threadIdx.x % kMergeLanes;
-  const int row = blockIdx.x * (kBlock / kMergeLanes) + threadIdx.x / kMergeLanes;
-  const bool live = row < a.R;  // every lane takes part in the shuffles
-  const int n = a.n_lse_chunks;
-  const rsrc_t pr = make_rsrc(a.lse_part + seg * n * a.R * 2, (uint64_t)n * a.R * 2 * sizeof(float));
-  auto off = [&](int c) { return (uint32_t)(((int64_t)c * a.R + row) * 8); };
-  float mx = -INFINITY;
-  if (live)
-    for (int c = lane; c < n; c += kMergeLanes) mx = fmaxf(mx, ldf(pr, off(c)));
-#pragma unroll
-  for (int o = 1; o < kMergeLanes; o <<= 1) mx = fmaxf(mx, __shfl_xor(mx, o, 64));
-  double sum = 0.0;
-  if (live && mx != -INFINITY) {
-    for (int c = lane; c < n; c += kMergeLanes) {
-      const uint64_t ms = ld64(pr, off(c));
-      const float mc = __uint_as_float((uint32_t)ms), sc = __uint_as_float((uint32_t)(ms >> 32));
-      if (mc != -INFINITY) sum += (double)sc * exp2((double)mc - (double)mx);
-    }
-  }
-#pragma unroll
-  for (int o = 1; o < kMergeLanes; o <<= 1) sum += __shfl_xor(sum, o, 64);
-  if (!live || lane != 0) return;
-  const float lse2 = (mx == -INFINITY || !(sum > 0.0)) ? -INFINITY : (float)((double)mx + log2(sum));
-  const rsrc_t lr = make_rsrc(a.lse2 + seg * a.R, (uint64_t)a.R * sizeof(float));
-  stf(lr, (uint32_t)row * 4u, lse2);
-}
 
 // Pass 2: window-summed probabilities of every scored key --------------------
 //
@@ -890,17 +440,6 @@ __global__ __launch_bounds__(kScoreBlock, 1) void colsum_keys_kernel(CompressArg
 }
 
 // Host-side dispatch ----------------------------------------------------------
-// Pass 1 (and its merge) with RBW row blocks per wave for its row split.
-template <typename T, int D, int RBW>
-static hipError_t launch_lse_t(const CompressArgs& a, hipStream_t st) {
-  const dim3 sblk(kScoreBlock);
-  SGDKV_LAUNCH("score_lse", (lse_kernel<T, D, RBW>), dim3(a.B * a.Hkv * a.lse_n_rsplit, a.n_lse_wgs), sblk, st, a);
-  constexpr int rows_per_wg = kBlock / kMergeLanes;
-  SGDKV_LAUNCH("lse_merge", lse_merge_kernel, dim3((unsigned)((a.R + rows_per_wg - 1) / rows_per_wg), a.B * a.Hkv),
-               dim3(kBlock), st, a);
-  return hipGetLastError();
-}
-
 // Pass 2 with RBW row blocks per wave for its row split.
 template <typename T, int D, int RBW>
 static hipError_t launch_colsum_t(const CompressArgs& a, hipStream_t st) {
@@ -934,49 +473,22 @@ static hipError_t launch_colsum_t(const CompressArgs& a, hipStream_t st) {
   return hipGetLastError();
 }
 
-// Row blocks per wave for a row split of `rows` rows (its largest split), as a template argument.
-template <typename T, int D, template <typename, int, int> class L>
-static hipError_t dispatch_rbw(int rows, const CompressArgs& a, hipStream_t st) {
-  const int nrb = (rows + 15) / 16;
-  switch ((nrb + kScoreWaves - 1) / kScoreWaves) {
-    case 1: return L<T, D, 1>::run(a, st);
-    case 2: return L<T, D, 2>::run(a, st);
-    case 3: return L<T, D, 3>::run(a, st);
-    case 4: return L<T, D, 4>::run(a, st);
-#if SGDKV_SCORE_WAVES_MAX_RBW > 4
-    case 5: return L<T, D, 5>::run(a, st);
-    case 6: return L<T, D, 6>::run(a, st);
-    case 7: return L<T, D, 7>::run(a, st);
-    case 8: return L<T, D, 8>::run(a, st);
-#endif
-    default: return hipErrorInvalidValue;
-  }
-}
-template <typename T, int D, int RBW>
-struct LseLaunch {
-  static hipError_t run(const CompressArgs& a, hipStream_t st) { return launch_lse_t<T, D, RBW>(a, st); }
-};
 template <typename T, int D, int RBW>
 struct ColsumLaunch {
   static hipError_t run(const CompressArgs& a, hipStream_t st) { return launch_colsum_t<T, D, RBW>(a, st); }
 };
 
-template <typename T, int D>
-static hipError_t launch_scores_d(const CompressArgs& a, hipStream_t st) {
+hipError_t launch_scores(const CompressArgs& a, hipStream_t st) {
   if (a.window_lse == nullptr) {
-    const hipError_t e = dispatch_rbw<T, D, LseLaunch>(a.lse_rs_rows, a, st);
+    const hipError_t e = launch_lse(a, st);
     if (e != hipSuccess) return e;
   }
-  return dispatch_rbw<T, D, ColsumLaunch>(a.rs_rows, a, st);
-}
-
-hipError_t launch_scores(const CompressArgs& a, hipStream_t st) {
   if (a.dtype == 1) {
-    if (a.D == 128) return launch_scores_d<__bf16, 128>(a, st);
-    if (a.D == 64) return launch_scores_d<__bf16, 64>(a, st);
+    if (a.D == 128) return dispatch_rbw<__bf16, 128, ColsumLaunch>(a.rs_rows, a, st);
+    if (a.D == 64) return dispatch_rbw<__bf16, 64, ColsumLaunch>(a.rs_rows, a, st);
   } else {
-    if (a.D == 128) return launch_scores_d<float, 128>(a, st);
-    if (a.D == 64) return launch_scores_d<float, 64>(a, st);
+    if (a.D == 128) return dispatch_rbw<float, 128, ColsumLaunch>(a.rs_rows, a, st);
+    if (a.D == 64) return dispatch_rbw<float, 64, ColsumLaunch>(a.rs_rows, a, st);
   }
   return hipErrorInvalidValue;
 }

@@ -110,6 +110,7 @@ struct CompressArgs {
   int copy_blocks = 0;              // gather work items per segment: ceil(max_h b_h / kCopyRows)
 };
 
+hipError_t launch_lse(const CompressArgs& a, hipStream_t stream);         // pass 1 and its merge
 hipError_t launch_scores(const CompressArgs& a, hipStream_t stream);      // passes 1 and 2
 hipError_t launch_select(const CompressArgs& a, bool scores_only, hipStream_t stream);  // pool .. compact
 // The row gather; max_blocks > 0 caps its grid (the copy then runs beside other work).

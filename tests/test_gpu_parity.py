@@ -218,6 +218,22 @@ def test_scores_with_long_chunks(B, C, Hq, Hkv, d, w, agg):
     _check_scores(g[[0, B - 1]].cpu().numpy(), orc["pooled"], "long chunks", rtol=_score_rtol(t["q_win"]))
 
 
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("G,w", [(2, 60), (4, 62), (6, 61), (8, 63)])
+def test_every_instance_of_pass_one(G, w, d, dtype):
+    """One to four row blocks per wave, both head dimensions and key types: each instance of pass 1 is
+    compiled in one of two files, whose rule the launch shares. Chunks of several tiles and a tail."""
+    B, Hkv, C = 2, 2, 5100
+    wl = workloads.Workload("lse", "lse", 1, G * Hkv, Hkv, d, C, w, 5, 0, 0, B, "bf16", 41, "beta")
+    t = workloads.torch_layer_tensors(wl, 0, DEV, dtype=dtype)
+    budgets = np.array([w + C // 3, C // 2])
+    _announce(f"pass 1 G={G} w={w} d={d} {dtype}")
+    res, orc = _compress_both(t["q_win"], t["k"], t["v"], budgets, kp=5, s=0, W=w)
+    _check_scores(res["scores"].cpu().numpy(), orc["pooled"], "pass 1", rtol=_score_rtol(t["q_win"]))
+    _check_kept(res, orc, t["q_win"].shape, C, w, 0, w, budgets, "pass 1", rtol=_score_rtol(t["q_win"]))
+
+
 @pytest.mark.parametrize("C,w,win0,dtype", [
     (640, 64, None, torch.bfloat16), (641, 64, 577, torch.bfloat16), (703, 63, None, torch.bfloat16),
     (767, 64, 640, torch.bfloat16), (900, 33, 900, torch.bfloat16), (1024, 16, 1024, torch.float32),
