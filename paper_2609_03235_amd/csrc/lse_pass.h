@@ -204,14 +204,15 @@ __global__ __launch_bounds__(kScoreBlock, 1) void lse_kernel(CompressArgs a) {
   // The uniform chunks of keys every row sees come first in the grid, then the short tail chunks, if
   // those have workgroups of their own (with both mixed segment by segment, some shader engines got
   // more long workgroups than they have compute units: 766 us for 420 at 128K x 8); otherwise the
-  // last uniform chunk's workgroup goes on to them. Keys past the last window row's position are
-  // seen by no row.
+  // last lse_tailers uniform chunks' workgroups go on to them, in turn. Keys past the last window
+  // row's position are seen by no row.
   const int chunk = (int)blockIdx.y;
   const int64_t key0 = (int64_t)chunk * a.lse_chunk;
   const int64_t key_end = key0 + a.lse_chunk < a.lse_tail0 ? key0 + a.lse_chunk : a.lse_tail0;
-  const int tail0 = chunk >= a.n_lse_head ? chunk : a.n_lse_head;  // tail chunks of this workgroup
-  const int tail1 = chunk >= a.n_lse_head ? chunk + 1
-                    : chunk == a.n_lse_head - 1 && (int)gridDim.y == a.n_lse_head ? a.n_lse_chunks : 0;
+  // tail chunks of this workgroup: tail0, tail0 + lse_tailers, ..
+  const int late = a.n_lse_head - 1 - chunk;  // uniform chunks after this one, or below 0
+  const int tail0 = late < 0 ? chunk : late < a.lse_tailers ? a.n_lse_head + late : a.n_lse_chunks;
+  const int tstep = late < 0 ? a.n_lse_chunks : a.lse_tailers;
   const int tid = threadIdx.x, wid = tid >> 6, lane = tid & 63;
   const int r0 = split * a.lse_rs_rows;
   const int nrows = a.R - r0 < a.lse_rs_rows ? a.R - r0 : a.lse_rs_rows;
@@ -223,7 +224,7 @@ __global__ __launch_bounds__(kScoreBlock, 1) void lse_kernel(CompressArgs a) {
   if (wid + kScoreWaves * (RBW - 1) < nrb) {
     if (chunk < a.n_lse_head)
       lse_chunk<T, D, RBW>(a, ktile, seg, chunk, r0, nrows, wid, lane, qa, kr, key0, key_end);
-    for (int c = tail0; c < tail1; ++c) lse_tail<T, D, RBW>(a, seg, c, r0, nrows, wid, lane, qa, kr);
+    for (int c = tail0; c < a.n_lse_chunks; c += tstep) lse_tail<T, D, RBW>(a, seg, c, r0, nrows, wid, lane, qa, kr);
   } else {
     Frag<T> qb[RBW > 1 ? RBW - 1 : 1][G::NC];
 #pragma unroll
@@ -232,7 +233,7 @@ __global__ __launch_bounds__(kScoreBlock, 1) void lse_kernel(CompressArgs a) {
       for (int c = 0; c < G::NC; ++c) qb[j][c] = qa[j][c];
     if (chunk < a.n_lse_head)
       lse_chunk<T, D, RBW - 1>(a, ktile, seg, chunk, r0, nrows, wid, lane, qb, kr, key0, key_end);
-    for (int c = tail0; c < tail1; ++c) lse_tail<T, D, RBW - 1>(a, seg, c, r0, nrows, wid, lane, qb, kr);
+    for (int c = tail0; c < a.n_lse_chunks; c += tstep) lse_tail<T, D, RBW - 1>(a, seg, c, r0, nrows, wid, lane, qb, kr);
   }
 }
 

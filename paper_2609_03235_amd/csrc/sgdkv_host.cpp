@@ -405,9 +405,12 @@ sgdkv_status plan_compress(const sgdkv_compress_desc* d, int64_t win0, CompressP
   // sees in uniform chunks (about one workgroup per CU), the rest (at most w + 127 keys) in short
   // tail chunks. Those get workgroups of their own (about 5 us each) where they run beside the
   // uniform chunks, at most one workgroup per CU in all, for which a uniform chunk may be a tile
-  // longer; run after them they cost the launch those 5 us (5 % at 100K x 1), so otherwise the
-  // last uniform chunk's workgroup, usually the shortest, does them. The chunk sizes depend on C and
-  // w only, so the workspace does not depend on win0.
+  // longer; run after them they cost the launch those 5 us (5 % at 100K x 1). Otherwise workgroups of
+  // uniform chunks do them after their own keys, where a tail chunk takes about two thirds of a tile's
+  // time (2 of 3.2 us): the last one's alone if it is shorter than the rest by a tile for each of them
+  // (100K x 1: pass 1 84 us, 88 with one each on the last seven), else one each on the last chunks'
+  // (128K x 8: 409 us, 415 with all four on the last). The chunk sizes depend on C and w only, so the
+  // workspace does not depend on win0.
   {
     const int64_t vis_end = std::min<int64_t>(a.C, win0 + a.w);
     const int64_t open_end = std::min<int64_t>(a.C, win0);
@@ -429,6 +432,9 @@ sgdkv_status plan_compress(const sgdkv_compress_desc* d, int64_t win0, CompressP
     a.n_lse_chunks = a.n_lse_head + (int)ceil_div(vis_end - a.lse_tail0, sgdkv::kLseTail);
     const bool own = nseg * a.n_rsplit * a.n_lse_chunks <= sgdkv::kScoreWorkgroups || a.n_lse_head == 0;
     a.n_lse_wgs = own ? a.n_lse_chunks : a.n_lse_head;
+    const int n_tails = a.n_lse_chunks - a.n_lse_head;
+    const int64_t spare = (a.n_lse_head * a.lse_chunk - a.lse_tail0) / sgdkv::kLseTile;  // tiles
+    a.lse_tailers = own ? 0 : spare >= n_tails ? 1 : std::min(n_tails, a.n_lse_head);
     p.lse_chunks_max = (int)(ceil_div(a.C, a.lse_chunk) + tails_max);
   }
   a.n_col_chunks = (int)ceil_div(a.n_scored, a.score_chunk);

@@ -97,8 +97,9 @@ struct CompressArgs {
   int64_t lse_tail0;
   int n_lse_head;
   int n_lse_chunks;     // n_lse_head + the tail chunks
-  int n_lse_wgs;        // workgroups per segment and row split: n_lse_chunks, or n_lse_head where the last
-                        // uniform chunk's workgroup does the tail chunks too
+  int n_lse_wgs;        // workgroups per segment and row split: n_lse_chunks, or n_lse_head where
+                        // uniform chunks' workgroups do the tail chunks too
+  int lse_tailers;      // how many of those (the last ones; 0: the tail chunks have workgroups of their own)
   int n_col_chunks;     // ceil(n_scored / score_chunk)
   int64_t hist_chunk;   // positions per pooling / radix-pass / compaction workgroup (multiple of 256)
   int n_hist_chunks;    // ceil(n_scored / hist_chunk): scored chunks

@@ -254,6 +254,29 @@ def test_window_lse_tail_chunks(C, w, win0, dtype):
     _check_kept(res, orc, t["q_win"].shape, C, w, 0, W, budgets, "lse tail", win0=win0, rtol=_score_rtol(t["q_win"]))
 
 
+@pytest.mark.parametrize("B,C,Hq,w,win0", [
+    (32, 1024, 14, 64, None), (40, 700, 14, 64, None), (33, 1300, 14, 16, None), (32, 1024, 8, 64, 1024),
+    (20, 900, 18, 64, None), (100, 1500, 4, 128, 1111)])
+def test_window_lse_tail_chunks_of_a_batch(B, C, Hq, w, win0):
+    """Batches whose tail chunks of pass 1 have no workgroups of their own: one each on the last uniform
+    chunks' workgroups, several each where the tails outnumber those, all on the last one where it is
+    short enough, none at all; with two row splits. Every sequence but the last repeats the first."""
+    Hkv, d = 2, 64
+    wl = workloads.Workload("tails", "tails", 1, Hq, Hkv, d, C, w, 5, 0, 0, 2, "bf16", 29, "beta")
+    t = workloads.torch_layer_tensors(wl, 0, DEV)
+    idx = torch.tensor([0] * (B - 1) + [1], device=DEV)
+    big = {n: t[n][idx].contiguous() for n in ("q_win", "k", "v")}
+    pos = -1 if win0 is None else win0
+    W = w if win0 is None else max(C - win0, 1)
+    _announce(f"batch tails B={B} C={C} Hq={Hq} w={w} win0={win0}")
+    g = sg.compress_layer(big["q_win"], big["k"], big["v"], None, pool_kernel=5, b_sink=0, b_window=W,
+                          scores_only=True, window_pos=pos)["scores"]
+    torch.cuda.synchronize()
+    orc = oracle.compress(_f64(t["q_win"]), _f64(t["k"]), _f64(t["v"]), np.full(Hkv, W), w=w, kp=5, s=0, W=W, win0=win0)
+    assert all(torch.equal(g[b], g[0]) for b in range(1, B - 1))
+    _check_scores(g[[0, B - 1]].cpu().numpy(), orc["pooled"], "batch tails", rtol=_score_rtol(t["q_win"]))
+
+
 @pytest.mark.parametrize("n,kp,ties,fixed", [
     (4, 7, False, (0, 32)), (255, 1, False, (4, 32)), (4095, 7, False, (4, 32)), (4097, 15, True, (4, 64)),
     (8192, 7, True, (4, 32)), (8193, 5, False, (0, 32)), (12289, 21, True, (128, 128)), (24571, 13, True, (4, 32)),
