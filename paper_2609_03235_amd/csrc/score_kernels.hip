@@ -283,7 +283,7 @@ __global__ __launch_bounds__(kScoreBlock, 1) void colsum_kernel(CompressArgs a) 
 
 // Pass 2 with the keys in registers -------------------------------------------
 //
-// For bf16 keys and chunks that give every wave several turns (all aggregations but Ipt. max): the
+// For bf16 keys and workgroups that give every wave seven turns or more (all aggregations but Ipt. max): the
 // window rows of the split sit in LDS, and each wave takes 64 keys at a time into registers, straight
 // from global memory (the next 64 in flight), and walks over all row blocks. A key's sum then stays in
 // its lanes until the end: no column partials in LDS, no barrier after the start, every wave all of
@@ -298,8 +298,8 @@ __global__ __launch_bounds__(kScoreBlock, 1) void colsum_kernel(CompressArgs a) 
 // x 4 x 8 heads of d 64 238 -> 207, 256K x 2 with a 32-token window 142 -> 121, 64K x 8 heads of d 64
 // with 128 rows 40 -> 32.
 constexpr int kKeyTurn = 64;  // keys of a wave's turn
-constexpr int kKeyChunkMin = 4096;       // keys of a chunk from which the turns are worth it
-constexpr int kKeyChunkMinTall = 32768;  // the same for more than sixteen row blocks
+constexpr int kKeyChunkMin = 3584;      // keys of a workgroup from which the turns are worth it
+constexpr int kKeyChunkMinTall = 6144;  // the same for more than sixteen row blocks
 
 template <typename T, int D>
 __global__ __launch_bounds__(kScoreBlock, 1) void colsum_keys_kernel(CompressArgs a) {
@@ -447,18 +447,16 @@ static hipError_t launch_colsum_t(const CompressArgs& a, hipStream_t st) {
   if (a.n_col_chunks > 0) {
     const dim3 cgrid(a.n_col_chunks, a.B * a.Hkv, a.n_rsplit);
     if constexpr (sizeof(T) == 2) {
-      // at least 8 turns of 64 keys per wave (100K x 2 x 8 heads of d 64, 6400-key chunks: 36 us
-      // against 43): shorter chunks lose to the last turns' spread and to filling the rows' LDS (32K x 1:
-      // 512-key chunks, 25 us against 22), Ipt. max to its reduction per head (100K x 1: 102 against 98),
-      // and three or four whole row blocks on every wave leave the tile kernel nothing uneven (64K x 4
-      // with 512 rows: the pass 362 us against 352-377 from box to box; with eight or sixteen blocks in
-      // all it reads the LDS too often: 64K x 8 with 128 rows of d 64, 40 us against 32)
-      // With more than sixteen row blocks the chip runs at its power limit, and up to 16384-key chunks
-      // what pass 2 gains the next pass 1 loses to the clock (128K x 8: pass 2 428-436 -> 407-430 us,
-      // pass 1 410 -> 444); at 1M x 4 (65536) the pass gains 4-5 %.
+      // The keys a workgroup has make the difference: short chunks lose to the last turns' spread and
+      // to filling the rows' LDS, the more rows the longer. Whole call, tiles / this: 128 rows at 2048
+      // keys 88.2 / 90.4 us, 4096 147.6 / 146.7, 8192 283.9 / 277.2, 256 rows at 2048 114.0 / 115.2, 3072 155.7 /
+      // 151.8, 16384 735 / 685; 448 rows at 4096 266.1 / 266.9, 6144 389.8 / 388.0, 16384 996 / 973, 49152
+      // 3071 / 2934; 512 rows at 6144 429.3 / 427.8, 8192 557 / 550, 16384 1103 / 1082 (1138 / 1116 on another
+      // card). A chunk holds no more keys than its segment: 256 sequences of 1024 keys, 256 rows, 312 / 332,
+      // 64 of 3072 161.7 / 157.9. Ipt. max loses to its reduction per head (100K x 1: 98 / 102 for the pass).
       const int nrb = (a.rs_rows + 15) / 16;
-      if (a.agg != 1 && a.score_chunk >= (nrb <= 16 ? kKeyChunkMin : kKeyChunkMinTall) &&
-          (nrb <= 16 || nrb % kScoreWaves != 0)) {
+      const int64_t keys = a.score_chunk < a.n_scored ? a.score_chunk : a.n_scored;
+      if (a.agg != 1 && keys >= (nrb <= 16 ? kKeyChunkMin : kKeyChunkMinTall)) {
         SGDKV_LAUNCH("score_colsum", (colsum_keys_kernel<T, D>), cgrid, sblk, st, a);
         return hipGetLastError();
       }

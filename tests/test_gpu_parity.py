@@ -196,23 +196,34 @@ def test_pool_kernel_widths(kp):
 @pytest.mark.parametrize("B,C,Hq,Hkv,d,w,agg", [
     (18, 32768, 28, 4, 128, 16, sg.GROUP_MEAN), (32, 32801, 4, 2, 64, 8, sg.GROUP_IPT_MEAN),
     (9, 65100, 8, 8, 64, 17, sg.GROUP_MEAN), (2, 140000, 16, 2, 128, 64, sg.GROUP_IPT_ONLY),
-    (2, 131072, 28, 4, 128, 128, sg.GROUP_MEAN)])
-def test_scores_with_long_chunks(B, C, Hq, Hkv, d, w, agg):
-    """Pass 2 with the keys in registers (chunks of 4096 keys and more): one to 32 row blocks (odd and
-    even, part blocks, two row splits), last turns of part keys. Every sequence repeats the first one's
-    tensors except the last, so the oracle runs on two of them; all of the others must match the first
-    bit for bit (their chunks are handed out in another order)."""
+    (2, 131072, 28, 4, 128, 128, sg.GROUP_MEAN), (6, 140000, 16, 2, 128, 64, sg.GROUP_IPT_ONLY),
+    (4, 100001, 20, 4, 64, 100, sg.GROUP_IPT_MEAN), (4, 66000, 20, 4, 64, 128, sg.GROUP_IPT_ONLY),
+    (8, 50011, 16, 4, 64, 68, sg.GROUP_MEAN), (64, 3700, 8, 4, 64, 32, sg.GROUP_MEAN),
+    (64, 3600, 8, 4, 64, 32, sg.GROUP_MEAN)])
+@pytest.mark.parametrize("given", [False, True])
+def test_scores_with_long_chunks(B, C, Hq, Hkv, d, w, agg, given):
+    """Pass 2 with the keys in registers (workgroups of 3584 keys and more, 6144 with more than sixteen
+    row blocks; 140000 x 2 and 3600 x 64 fall just short and take the tiles): one to 32 row blocks (odd
+    and even, part blocks, two row splits), last turns of part keys, with the window rows' LSE computed
+    or given. Every sequence repeats the first one's tensors except the last, so the oracle runs on two
+    of them; all of the others must match the first bit for bit (their chunks are handed out in another
+    order)."""
     wl = workloads.Workload("long", "long", 1, Hq, Hkv, d, C, w, 7, 4, w, 2, "bf16", 23, "beta")
     t = workloads.torch_layer_tensors(wl, 0, DEV)
     idx = torch.tensor([0] * (B - 1) + [1], device=DEV)
     big = {n: t[n][idx].contiguous() for n in ("q_win", "k", "v")}
     sig = np.random.Generator(np.random.PCG64(5)).uniform(0.1, 1.0, size=Hq)
-    _announce(f"long chunks B={B} C={C} Hq={Hq} Hkv={Hkv} d={d} w={w} agg={agg}")
+    lse = None
+    if given:  # each row off by a constant of its own, so that the computed one would show
+        lse = oracle.window_lse(_f64(t["q_win"]), _f64(t["k"])) + np.linspace(-0.5, 0.5, Hq * w).reshape(1, Hq, w)
+        lse = torch.from_numpy(lse).float().to(DEV)
+    _announce(f"long chunks B={B} C={C} Hq={Hq} Hkv={Hkv} d={d} w={w} agg={agg} given={given}")
     res = sg.compress_layer(big["q_win"], big["k"], big["v"], None, pool_kernel=7, b_sink=4, b_window=w,
-                            scores_only=True, group_agg=agg, qhead_scores=sig)
+                            scores_only=True, group_agg=agg, qhead_scores=sig,
+                            window_lse=lse[idx].contiguous() if given else None)
     torch.cuda.synchronize()
     orc = oracle.compress(_f64(t["q_win"]), _f64(t["k"]), _f64(t["v"]), np.full(Hkv, 4 + w), w=w, kp=7, s=4, W=w,
-                          agg=agg, qhead_scores=sig)
+                          agg=agg, qhead_scores=sig, lse=_f64(lse) if given else None)
     g = res["scores"]
     assert all(torch.equal(g[b], g[0]) for b in range(1, B - 1))
     _check_scores(g[[0, B - 1]].cpu().numpy(), orc["pooled"], "long chunks", rtol=_score_rtol(t["q_win"]))
