@@ -865,6 +865,8 @@ __global__ __launch_bounds__(kBlock) void copy_rows_kernel(CompressArgs a) {
 }
 
 // Pooling (+ the digit-0 histogram) with the width built in where one is.
+constexpr int kPoolBuiltIn = 15;  // pooling widths up to this are template arguments
+
 template <bool HIST>
 static void launch_pool(const CompressArgs& a, dim3 grid, hipStream_t st) {
   const dim3 blk(kBlock);
@@ -884,8 +886,8 @@ static void launch_pool(const CompressArgs& a, dim3 grid, hipStream_t st) {
 
 template <int CAP>
 static void launch_select_segment(const CompressArgs& a, hipStream_t st) {
-  // shares of the write-out: as many as the segments leave compute units for, at most eight (32K x 1
-  // x 4 heads: 27 us against 30 with one)
+  // shares of the write-out: as many as the segments leave compute units for, at most eight (event
+  // pairs around the launch, 32K x 1 x 4 heads: 22.1 us against 25.3 with one, 8K 13.2 / 13.8)
   int parts = 1;
   while (parts < 8 && a.B * a.Hkv * parts * 2 <= kScoreWorkgroups) parts *= 2;
   const dim3 grid(a.B * a.Hkv, parts), blk(kSegBlock);
@@ -902,18 +904,33 @@ static void launch_select_segment(const CompressArgs& a, hipStream_t st) {
   }
 }
 
+// Whole segments per workgroup while their scores fit its LDS and registers, for the built-in pooling
+// widths at nearly every size and batch up to there (pooling to compaction per layer, this / the
+// passes: 8K x 16 x 4 heads 13.8 / 39.5 us, 32K x 1 x 4 21.8 / 36.5, 32K x 8 x 4 24 / 46, 32K x 64 x 4 34 /
+// 96, event pairs around each launch included); a 64K segment would take twice a 32K one's time, where
+// the passes spread it over the device. The exceptions, timed as whole calls:
+//   Thousands of short segments: a workgroup of 1024 threads takes about 11 us whatever it holds, the
+// passes share compute units by the key (512 keys x 1024 segments 90.8 / 92.7 us, x 2048 157.2 / 151.3, x 4096
+// 299.5 / 281.1; 1024 keys x 2048 200.2 / 200.2, x 4096 421.6 / 407.2; 2048 keys x 4096 636.0 / 636.3).
+//   Other widths: a tap costs a 4-byte LDS read per position, in one compute unit per segment; the passes
+// spread that over the device, and take longer themselves where the segments are many (12K keys x 4 heads,
+// width 65: 43.4 / 46.6 us, 129: 56.2 / 48.0; 16K x 4, 33: 42.6 / 43.4, 65: 51.6 / 44.2; 24K x 8, 17: 49.6 /
+// 50.6, 21: 53.7 / 51.2; 32K x 4, 17: 51.7 / 49.3; 32K x 32, 21: 95.3 / 92.6; 32K x 128, 33: 266 / 277, 65: 284 /
+// 283; 16K x 128, 65: 144 / 152, 129: 162 / 161; 32K x 256, 65: 532 / 557).
+static bool select_by_segment(const CompressArgs& a) {
+  const int64_t n = a.n_scored, nseg = (int64_t)a.B * a.Hkv;
+  if (n > kSegScoredMax || (a.kp - 1) / 2 > kPoolHalo) return false;
+  if (nseg > 1024 && nseg > 2 * n) return false;
+  return a.kp <= kPoolBuiltIn || n * (a.kp + 32) <= 1200000 + 12000 * nseg;
+}
+
 hipError_t launch_select(const CompressArgs& a, bool scores_only, hipStream_t st) {
   const int nseg = a.B * a.Hkv;
   const dim3 blk(kBlock);
   if (a.n_col_chunks == 0) SGDKV_LAUNCH("select_init", select_init_kernel, dim3(nseg), blk, st, a);
   const dim3 hgrid(a.n_hist_chunks, nseg);
   const bool cands = a.C - a.s - a.W > 0;
-  // Whole segments per workgroup while their scores fit its LDS and registers: faster at every size
-  // and batch up to there (pooling to compaction per layer, this / the passes below: 8K x 16 x 4
-  // heads 13.8 / 39.5 us, 32K x 1 x 4 21.8 / 36.5, 32K x 8 x 4 24 / 46, 32K x 64 x 4 34 / 96,
-  // event pairs around each launch included); a 64K segment would take twice a 32K one's time,
-  // where the passes spread it over the device.
-  if (!scores_only && a.n_scored <= kSegScoredMax && (a.kp - 1) / 2 <= kPoolHalo) {
+  if (!scores_only && select_by_segment(a)) {
     if (a.n_scored <= kSegScoredMax / 4) launch_select_segment<kSegScoredMax / 4>(a, st);
     else launch_select_segment<kSegScoredMax>(a, st);
     return hipGetLastError();

@@ -312,6 +312,56 @@ def test_selection_by_segment_size(n, kp, ties, fixed):
         _check_gather(res, t["k"], t["v"], budgets)
 
 
+@pytest.mark.parametrize("kp", [1, 3, 5, 9, 11, 13, 15, 17, 129])
+@pytest.mark.parametrize("n", [4001, 9001, 32767, 32769])
+def test_pool_widths_on_both_routes(n, kp):
+    """Every built-in pooling width and two others, in the workgroup that selects a whole segment (up to
+    32768 scored keys; 129 only at 4001, 17 not at 32767) and in the passes, the second segment's rows
+    unaligned. The pooled scores of a scores-only call (always the passes) are the same bit for bit."""
+    B, w, (s, W) = 1, 32, (4, 40)
+    C = n + w
+    wl, t = _tiny_inputs(B=B, C=C, seed=n + kp)
+    budgets = np.array([s + W + n // 3, s + W + 7])
+    _announce(f"pool width {kp} n={n}")
+    res, orc = _compress_both(t["q_win"], t["k"], t["v"], budgets, kp=kp, s=s, W=W)
+    only = sg.compress_layer(t["q_win"], t["k"], t["v"], None, pool_kernel=kp, b_sink=s, b_window=W, scores_only=True)
+    assert torch.equal(res["scores"], only["scores"])
+    _check_scores(res["scores"].cpu().numpy(), orc["pooled"], f"pool {kp} {n}")
+    _check_kept(res, orc, t["q_win"].shape, C, w, s, W, budgets, f"pool {kp} {n}")
+    _check_gather(res, t["k"], t["v"], budgets)
+
+
+@pytest.mark.parametrize("B,n,kp", [
+    (512, 500, 7), (520, 500, 7), (520, 519, 7), (520, 520, 7), (1, 16384, 33), (1, 16385, 65), (1, 24576, 17),
+    (1, 24576, 21), (130, 16384, 65)])
+def test_selection_routes_by_segment_count(B, n, kp):
+    """Around the lines between the two selections: many short segments (more than 1024 and more than
+    two per scored key) and widths without a built-in form. Every sequence but the last repeats the
+    first, so the oracle runs on two of them."""
+    w, (s, W) = 32, (4, 40)
+    C = n + w
+    wl, t = _tiny_inputs(B=2, C=C, seed=n + kp)
+    idx = torch.tensor([0] * (B - 1) + [1], device=DEV)
+    big = {x: t[x][idx].contiguous() for x in ("q_win", "k", "v")}
+    budgets = np.array([s + W + n // 3, s + W + 7])
+    _announce(f"selection route B={B} n={n} kp={kp}")
+    res = sg.compress_layer(big["q_win"], big["k"], big["v"], budgets, pool_kernel=kp, b_sink=s, b_window=W)
+    torch.cuda.synchronize()
+    pick = [0, B - 1]
+    T = int(budgets.sum())
+    rows = lambda x: x.view(B, T, *x.shape[1:])
+    assert all(torch.equal(rows(res[x])[b], rows(res[x])[0]) for x in ("kept_pos", "k_c", "v_c") for b in range(B - 1))
+    offs = sg.segment_offsets(budgets, 2)
+    two = dict(offsets=torch.from_numpy(offs), offsets_host=offs, kept_pos=rows(res["kept_pos"])[pick].reshape(-1), k_c=rows(res["k_c"])[pick].reshape(2 * T, -1),
+               v_c=rows(res["v_c"])[pick].reshape(2 * T, -1), scores=res["scores"][pick])
+    orc = oracle.compress(_f64(big["q_win"][pick]), _f64(big["k"][pick]), _f64(big["v"][pick]), budgets, w=w, kp=kp,
+                          s=s, W=W)
+    q2, k2, v2 = (big[x][pick].contiguous() for x in ("q_win", "k", "v"))
+    _check_scores(two["scores"].cpu().numpy(), orc["pooled"], f"route {B} {n}")
+    _check_kept(two, orc, q2.shape, C, w, s, W, budgets, f"route {B} {n}")
+    _check_gather(two, k2, v2, budgets)
+
+
 @pytest.mark.parametrize("n,kp,fixed,one", [
     (5, 1, (2, 34), True), (4097, 7, (2048, 2080), True), (36, 1, (0, 32), False), (1029, 7, (4, 36), False),
     (8192, 1, (0, 32), False), (8193, 21, (16, 64), False), (32768, 7, (1024, 1024), False)])
