@@ -768,7 +768,10 @@ struct DecodePlan {
   size_t bytes;
 };
 
-sgdkv_status plan_decode(const sgdkv_decode_desc* d, const int64_t* offsets_host, int64_t capacity, DecodePlan& p) {
+// The plan of a call with n_new appended rows per segment; its workspace size and slots are those of any
+// number of them up to the capacity.
+sgdkv_status plan_decode(const sgdkv_decode_desc* d, const int64_t* offsets_host, int64_t capacity, int64_t n_new,
+                         DecodePlan& p) {
   if (!d) return fail(SGDKV_ERR_INVALID_ARG, "NULL descriptor");
   if (capacity < 0) return fail(SGDKV_ERR_INVALID_ARG, "capacity %lld < 0", (long long)capacity);
   if (!offsets_host) return fail(SGDKV_ERR_INVALID_ARG, "NULL offsets_host");
@@ -815,76 +818,116 @@ sgdkv_status plan_decode(const sgdkv_decode_desc* d, const int64_t* offsets_host
   // kDecodeMinChunk rows; one round of longer splits measured slower
   a.chunk = std::min<int64_t>(
       std::max<int64_t>(round_up(ceil_div(total - offsets_host[0], kDecodeSplits), 64), kDecodeMinChunk), 1 << 24);
-  // A cache small enough gets the shortest splits (of at least 64 rows) that launch at most one
-  // workgroup per compute unit, with room for one of appended rows per segment (up to 32; whatever
-  // the capacity, so that a call without appended rows does not depend on it): two workgroups on one
-  // unit take nearly twice as long as one, and 64-row splits at any count (or 128-row ones past 256
-  // workgroups) left units with two beside units with one. Decode per call, so chosen / as before:
-  // 143K rows 20.6 / 28.2 us, 168K 24.9 / 31.4, 106K 19.3 / 23.7, 264K 31.0 / 35.5, 318K 33.0 / 36.3.
-  // Past 320 rows a split two rounds of shorter ones are as fast (287K rows: 288 rows 35.4, 320
-  // 31.3, two rounds 33.9). Below 64 rows the partials to combine cost more than the shorter splits
-  // save (39K rows: 48 rows 15.0, 64 14.5). A filled segment takes a workgroup at any split length, so
-  // more of those than units leave nothing to look for (256 segments of 150 rows: 4 us of host time
-  // per plan, 18 with every length tried).
-  // One that would launch more than two rounds gets splits twice as long (fewer workgroups, each with
-  // less of its fixed cost per row, and fewer partials to combine: decode per 128K x B 8 layer -3.7 %;
-  // the 256K x B 16 and 1M x B 32 caches already have splits of 512 rows and more)
-  const int wpw = sgdkv::kDecodeWaves;  // splits (waves) per decode workgroup
-  if (a.chunk == kDecodeMinChunk) {
-    auto workgroups = [&](int64_t chunk) {  // never more for longer splits
-      const uint32_t rows = (uint32_t)(chunk * wpw);
-      int64_t n = 0;
-      for (int64_t i = 0; i < nseg; ++i)  // a segment's rows fit 32 bits with room (it holds at most 4 GiB)
-        n += ((uint32_t)(offsets_host[i + 1] - offsets_host[i]) + rows - 1) / rows;
-      return n;
-    };
-    const int64_t units = sgdkv::kScoreWorkgroups - std::min<int64_t>(nseg, sgdkv::kScoreWorkgroups / 8);
-    // c: the shortest length in steps of 16 rows that fits, past kDecodeUnitChunk if none does
-    int64_t c = std::max<int64_t>(round_up(ceil_div(total - offsets_host[0], units * wpw), 16), kDecodeMinChunk / 2);
-    if (filled > units || (c <= kDecodeUnitChunk && workgroups(kDecodeUnitChunk) > units)) {
-      c = kDecodeUnitChunk + 16;
-    } else if (c < kDecodeUnitChunk && workgroups(c) > units) {
-      int64_t fits = kDecodeUnitChunk;  // c does not
-      while (fits - c > 16) {
-        const int64_t mid = c + (fits - c) / 32 * 16;
-        (workgroups(mid) > units ? c : fits) = mid;
-      }
-      c = fits;
-    }
-    if (c <= kDecodeUnitChunk) a.chunk = c;
-    else if (workgroups(a.chunk) > 2 * kDecodeResident) a.chunk = kDecodeMinChunk * 2;
-  }
-  a.n_chunk_max = (int)ceil_div(longest, a.chunk);
+  a.cap = capacity;
   if ((int64_t)a.B * a.Hkv * capacity * rb > 0xFFFFFFFFll)
     return fail(SGDKV_ERR_UNSUPPORTED, "appended regions of %lld rows per head exceed 4 GiB", (long long)capacity);
-  a.cap = capacity;
-  a.n_cwg = (int)ceil_div(a.n_chunk_max, wpw);
-  // one partial slot per launched workgroup: with the compact grid each segment's own
-  // workgroups (so the workspace follows the total of the splits, not the longest segment),
-  // otherwise n_cwg per segment; plus the workgroups of a full appended region
-  const int64_t new_wg_cap = ceil_div(ceil_div(capacity, a.chunk), wpw);
-  if (nseg <= sgdkv::kMaxCompactSegs) {
+  const int wpw = sgdkv::kDecodeWaves;  // splits (waves) per decode workgroup
+  auto workgroups = [&](int64_t chunk) {  // never more for longer splits
+    const uint32_t rows = (uint32_t)(chunk * wpw);
+    int64_t n = 0;
+    for (int64_t i = 0; i < nseg; ++i)  // a segment's rows fit 32 bits with room (it holds at most 4 GiB)
+      n += ((uint32_t)(offsets_host[i + 1] - offsets_host[i]) + rows - 1) / rows;
+    return n;
+  };
+  auto appended_wgs = [&](int64_t n, int64_t chunk) { return ceil_div(ceil_div(n, chunk), wpw); };  // per segment
+  // Partial slots of splits of `chunk` rows, one per launched workgroup: with the compact grid each
+  // segment's own workgroups (so the workspace follows the total of the splits, not the longest
+  // segment), otherwise `cwg` per segment; plus the workgroups of a full appended region. cwg: the
+  // most workgroups a segment's compressed rows get. On the compact grid a segment's appended-row
+  // workgroups are numbered from there on, also where whole rounds gave it more than its splits need.
+  auto slots_of = [&](int64_t chunk, int64_t& cwg) {
+    const int64_t new_wg_cap = appended_wgs(capacity, chunk);
+    cwg = ceil_div(ceil_div(longest, chunk), wpw);
+    if (nseg > sgdkv::kMaxCompactSegs) return nseg * (cwg + new_wg_cap);
+    const int64_t w0 = workgroups(chunk);
+    if (w0 <= kDecodeResident) return w0 + nseg * new_wg_cap;
     // the most slots and compressed-row workgroups of any call with up to new_wg_cap appended
     // workgroups per segment (appended ones count toward the rounds only while they fit in half
     // a round: past that the plan is the one without them)
-    int64_t slots = 0, most = 0;
+    int64_t slots = 0;
     const int64_t k_fold = std::min<int64_t>(new_wg_cap, kDecodeResident / 2 / nseg);
     for (int64_t k = 0; k <= k_fold + 1 && k <= new_wg_cap; ++k) {
       const int64_t kk = k <= k_fold ? k : new_wg_cap;
-      int64_t s = 0;
-      for (const int64_t n : compact_workgroups(offsets_host, nseg, a.chunk, kk)) {
-        s += n + kk;
-        most = std::max(most, n);
+      int64_t n_k = 0;
+      for (const int64_t n : compact_workgroups(offsets_host, nseg, chunk, kk)) {
+        n_k += n + kk;
+        cwg = std::max(cwg, n);
       }
-      slots = std::max(slots, s);
+      slots = std::max(slots, n_k);
     }
-    a.n_slots = slots;
-    // a segment's appended-row workgroups are numbered from n_cwg on: past its compressed-row
-    // workgroups, also where whole rounds gave a segment more of them than its splits need
-    a.n_cwg = (int)std::max<int64_t>(a.n_cwg, most);
-  } else {
-    a.n_slots = nseg * (a.n_cwg + new_wg_cap);
+    return slots;
+  };
+  int64_t cwg = 0, slots = 0;
+  bool one = false;  // at most one workgroup of compressed rows per compute unit
+  // A cache small enough gets the shortest splits (of at least 64 rows, in steps of 16) that launch at
+  // most one workgroup per compute unit: two workgroups on one unit take nearly twice as long as one,
+  // and 64-row splits at any count (or 128-row ones past 256 workgroups) left units with two beside
+  // units with one. Decode per call, so chosen / as before: 143K rows 20.6 / 28.2 us, 106K 19.3 / 23.7,
+  // 264K 31.0 / 35.5, 318K 33.0 / 36.3. Past 320 rows a split two rounds of shorter ones are as fast
+  // (287K rows: 288 rows 35.4, 320 31.3, two rounds 33.9). Below 64 rows the partials to combine cost
+  // more than the shorter splits save (39K rows: 48 rows 15.0, 64 14.5). A filled segment takes a
+  // workgroup at any split length, so more of those than units leave nothing to look for (256 segments
+  // of 150 rows: 4 us of host time per plan, 18 with every length tried).
+  // Without appended rows the splits do not depend on the capacity; room is left for one workgroup
+  // of appended rows per segment, up to 32, so that batches of up to 32 segments decode their first
+  // token like the next ones. With appended rows every segment launches workgroups for them, which
+  // count (44 segments, 170K rows and 33 appended ones each: 27.7 us, without counting them 37.6, before 31.7).
+  // If no split length of up to 320 rows fits them, shorter splits in more workgroups are the faster: 64
+  // rows where 128 would leave units idle, else 128; 64 also where those alone fit (128 segments of 470
+  // rows: 25.3 us, 26.6 with 128 rows).
+  // A cache that launches more than two rounds gets splits twice as long (fewer workgroups, each with
+  // less of its fixed cost per row, and fewer partials to combine: decode per 128K x B 8 layer -3.7 %;
+  // the 256K x B 16 and 1M x B 32 caches already have splits of 512 rows and more)
+  if (a.chunk == kDecodeMinChunk) {
+    constexpr int64_t kUnits = sgdkv::kScoreWorkgroups;
+    const int64_t rows = total - offsets_host[0], room = kUnits - std::min<int64_t>(nseg, kUnits / 8);
+    const int64_t fewest = filled <= room ? workgroups(kDecodeUnitChunk) : room + 1;
+    if (fewest <= room) {
+      // the shortest split that launches at most `units` workgroups with those of n appended rows per
+      // segment (the longest one does)
+      auto one_round = [&](int64_t units, int64_t n) {
+        auto fits = [&](int64_t c) { return workgroups(c) + nseg * appended_wgs(n, c) <= units; };
+        int64_t c = std::max<int64_t>(round_up(ceil_div(rows, kUnits * wpw), 16), kDecodeMinChunk / 2);
+        if (c >= kDecodeUnitChunk || fits(c)) return std::min(c, kDecodeUnitChunk);
+        int64_t ok = kDecodeUnitChunk;  // fits; c does not
+        while (ok - c > 16) {
+          const int64_t mid = c + (ok - c) / 32 * 16;
+          (fits(mid) ? ok : c) = mid;
+        }
+        return ok;
+      };
+      // The workspace of a capacity holds the slots of either plan for any number of appended rows: at
+      // most those of the shortest splits. (Where that would take it past the static scratch, and
+      // beyond the compact grid, the appended rows do not count.)
+      int64_t n = 0;
+      if (capacity > 0 && nseg <= sgdkv::kMaxCompactSegs) {
+        const int64_t most =
+            rows / (kDecodeMinChunk / 2 * wpw) + filled + nseg * appended_wgs(capacity, kDecodeMinChunk / 2);
+        if ((size_t)most * G * (a.D + 2) * sizeof(float) <= sgdkv::kDecodeScratchBytes) {
+          slots = std::max(most, kUnits);
+          n = std::min(n_new, capacity);
+        }
+      }
+      one = n <= 0 || fewest + nseg * appended_wgs(n, kDecodeUnitChunk) <= kUnits;
+      if (n > 0 && workgroups(kDecodeMinChunk / 2) <= kUnits)
+        a.chunk = kDecodeMinChunk / 2, one = true;  // (appended rows beside such short ones cost little)
+      else if (one)
+        a.chunk = n <= 0 ? one_round(room, 0) : one_round(kUnits, n);
+      else if (workgroups(kDecodeMinChunk) < kUnits)
+        a.chunk = kDecodeMinChunk / 2;
+    } else if (workgroups(a.chunk) > 2 * kDecodeResident) {
+      a.chunk = kDecodeMinChunk * 2;
+    }
   }
+  if (slots > 0 && one) {
+    cwg = ceil_div(ceil_div(longest, a.chunk), wpw);
+  } else {
+    const int64_t own = slots_of(a.chunk, cwg);
+    if (slots == 0) slots = own;
+  }
+  a.n_chunk_max = (int)ceil_div(longest, a.chunk);
+  a.n_cwg = (int)cwg;
+  a.n_slots = slots;
   p.bytes = align256((size_t)a.n_slots * G * (a.D + 2) * sizeof(float));
   return SGDKV_OK;
 }
@@ -902,7 +945,7 @@ sgdkv_status sgdkv_decode_workspace_size_ex(const sgdkv_decode_desc* desc, const
                                             int64_t capacity, size_t* bytes) {
   if (!bytes) return fail(SGDKV_ERR_INVALID_ARG, "NULL bytes");
   DecodePlan p;
-  if (sgdkv_status st = plan_decode(desc, offsets_host, capacity, p)) return st;
+  if (sgdkv_status st = plan_decode(desc, offsets_host, capacity, 0, p)) return st;
   *bytes = p.bytes;
   return ok();
 }
@@ -929,7 +972,7 @@ sgdkv_status decode_step(const sgdkv_decode_desc* desc, const void* q, const voi
   const sgdkv_decode_tail none{nullptr, nullptr, 0, 0};
   const sgdkv_decode_tail& t = tail ? *tail : none;
   DecodePlan p;
-  if (sgdkv_status st = plan_decode(desc, offsets_host, t.capacity, p)) return st;
+  if (sgdkv_status st = plan_decode(desc, offsets_host, t.capacity, t.n_new, p)) return st;
   sgdkv::DecodeArgs& a = p.a;
   if (t.n_new < 0 || t.n_new > t.capacity)
     return fail(SGDKV_ERR_INVALID_ARG, "n_new %lld outside [0, capacity %lld]", (long long)t.n_new,
@@ -1020,7 +1063,7 @@ sgdkv_status sgdkv_append_kv(const sgdkv_decode_desc* desc, const void* k_step, 
   // plan with empty segments: checks the sizes and the bound of the appended region
   const std::vector<int64_t> offs((size_t)nseg + 1, 0);
   DecodePlan p;
-  if (sgdkv_status st = plan_decode(desc, offs.data(), capacity, p)) return st;
+  if (sgdkv_status st = plan_decode(desc, offs.data(), capacity, 0, p)) return st;
   if (slot < 0 || slot >= capacity)
     return fail(SGDKV_ERR_INVALID_ARG, "slot %lld outside [0, capacity %lld)", (long long)slot, (long long)capacity);
   const void* ptrs[] = {k_step, v_step, k_new, v_new};

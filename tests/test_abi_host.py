@@ -494,23 +494,51 @@ def test_decode_planning_time_of_many_short_segments():
     assert best(2) < 3 * best(0)
 
 
-@pytest.mark.parametrize("lens", [[143000 // 32] * 32, [20000, 0, 17, 60000], [1] * 224, [1] * 225, [1279] * 224,
-                                  [1281] * 224, [3000, 40] * 40, [0, 300000], [286720 // 4] * 4, [64] * 512])
-@pytest.mark.parametrize("cap", [0, 300])
-def test_decode_split_length_of_small_caches(lens, cap):
-    """The plan takes the shortest splits of 64 to 320 rows, in steps of 16, that launch at most a
-    workgroup (four splits) per compute unit less room for a segment's appended rows; if none does, 128
-    rows, or 256 where those launch more than two rounds."""
+SMALL_CACHES = [[143000 // 32] * 32, [20000, 0, 17, 60000], [1] * 224, [1] * 225, [1279] * 224, [1281] * 224,
+                [3000, 40] * 40, [0, 300000], [286720 // 4] * 4, [64] * 512]
+
+
+def _small_cache_splits(lens, n_new):
+    """The split length of a small cache: the shortest of 64 to 320 rows, in steps of 16, that launches at
+    most a workgroup (four splits) per compute unit, with those of the appended rows (without any, room
+    for one per segment, up to 32); None if there is none."""
+    n = len(lens)
+    units, per = (256, lambda c: -(-n_new // (4 * c))) if n_new else (256 - min(n, 32), lambda c: 0)
+    fits = [c for c in range(64, 321, 16) if sum(-(-l // (4 * c)) for l in lens) + n * per(c) <= units]
+    return fits[0] if fits else None
+
+
+@pytest.mark.parametrize("lens", SMALL_CACHES)
+def test_decode_split_length_of_small_caches(lens):
+    """If no split length launches one round, splits of 128 rows, or 256 where those launch more than two."""
     G, d, n = 7, 128, len(lens)
     desc = sg.DecodeDesc(1, n * G, n, d, sg.DTYPE_BF16, sg.DTYPE_F32, 0.0)
     oh = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
     wgs = lambda c: int(sum(-(-l // (4 * c)) for l in lens))
-    units = 256 - min(n, 32)
-    fits = [c for c in range(64, 321, 16) if wgs(c) <= units]
-    chunk = fits[0] if fits else 256 if wgs(128) > 1024 else 128
+    chunk = _small_cache_splits(lens, 0) or (256 if wgs(128) > 1024 else 128)
     if wgs(chunk) <= 512:  # past one round the workgroups are shared out over whole rounds
-        slots = wgs(chunk) + n * -(-cap // (4 * chunk))
-        assert sg.decode_workspace_size(desc, oh, cap) == -(-slots * G * (d + 2) * 4 // 256) * 256
+        assert sg.decode_workspace_size(desc, oh) == -(-wgs(chunk) * G * (d + 2) * 4 // 256) * 256
+
+
+@pytest.mark.parametrize("lens", SMALL_CACHES + [[2650] * 64, [5650] * 44, [3600] * 64, [470] * 128, [300] * 200])
+@pytest.mark.parametrize("cap", [1, 64, 300, 3000])
+def test_decode_workspace_of_small_caches_covers_every_appended_count(lens, cap):
+    """With appended rows the splits are of 64 rows if those alone launch one round, else the shortest that
+    do with the workgroups of the appended rows, else 64 rows where 128 would leave units idle, else 128: the workspace of a capacity holds the
+    slots of every count of appended rows up to it, and of the plan without any."""
+    G, d, n = 7, 128, len(lens)
+    desc = sg.DecodeDesc(1, n * G, n, d, sg.DTYPE_BF16, sg.DTYPE_F32, 0.0)
+    oh = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+    wgs = lambda c: int(sum(-(-l // (4 * c)) for l in lens))
+    plain = _small_cache_splits(lens, 0)
+    slots = sg.decode_workspace_size(desc, oh, cap) // (G * (d + 2) * 4)
+    assert slots >= sg.decode_workspace_size(desc, oh) // (G * (d + 2) * 4)
+    for n_new in sorted({1, 33, 64, cap // 2, cap} & set(range(1, cap + 1))):
+        c = (64 if wgs(64) <= 256 else _small_cache_splits(lens, n_new)) if plain else None
+        if c is None:
+            c = (64 if wgs(128) < 256 else 128) if plain else 256 if wgs(128) > 1024 else 128
+        if wgs(c) <= 512:
+            assert slots >= wgs(c) + n * -(-n_new // (4 * c)), (n_new, c)
 
 
 def test_decode_workspace_with_appended_rows():

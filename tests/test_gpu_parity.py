@@ -831,6 +831,42 @@ def test_decode_one_workgroup_per_unit(G, d, dtype, rows, cap):
         assert (lse[0, sl].double() - torch.logsumexp(logits, 1)).abs().max() <= 1e-5
 
 
+@pytest.mark.parametrize("B,Hkv,rows,cap", [(11, 4, 2500, 64), (16, 4, 3600, 300), (12, 8, 1770, 40), (2, 2, 30000, 3000),
+                                            (25, 8, 300, 64), (130, 4, 20, 5)])
+def test_decode_plan_with_appended_rows(B, Hkv, rows, cap):
+    """Caches of up to a workgroup per compute unit whose splits depend on the number of appended rows:
+    counts that fit one round with them, that do not, and none, one after the other on the workspace of
+    the capacity; segments of unequal lengths."""
+    G, d = 2, 64
+    nseg = B * Hkv
+    lens = np.array([rows + (i * 37) % 101 - 50 if rows > 60 else (i * 7) % (2 * rows) for i in range(nseg)], dtype=np.int64)
+    offs = np.concatenate([[0], np.cumsum(lens)])
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(rows + cap)
+    mk = lambda *shape: torch.randn(shape, generator=gen, device=DEV).to(torch.bfloat16)
+    kc, vc, q = mk(int(offs[-1]), d), mk(int(offs[-1]), d), mk(B, Hkv * G, d)
+    k_new, v_new = mk(B, Hkv, cap, d), mk(B, Hkv, cap, d)
+    offs_d = torch.from_numpy(offs).to(DEV)
+    desc = sg.decode_desc(q, Hkv, torch.float32)
+    ws = sg.alloc_workspace(sg.decode_workspace_size(desc, offs, cap), DEV)
+    for n_new in (cap, 1, 0, cap // 2):
+        _announce(f"decode plan B={B} Hkv={Hkv} rows={rows} cap={cap} n_new={n_new}")
+        out, lse = sg.decode_attention(q, kc, vc, offs_d, offs, Hkv, out_dtype=torch.float32, workspace=ws,
+                                       k_new=k_new, v_new=v_new, n_new=n_new)
+        for s in range(nseg):
+            b, h = divmod(s, Hkv)
+            k = torch.cat([kc[offs[s]:offs[s + 1]], k_new[b, h, :n_new]]).double()
+            v = torch.cat([vc[offs[s]:offs[s + 1]], v_new[b, h, :n_new]]).double()
+            sl = slice(h * G, (h + 1) * G)
+            if k.shape[0] == 0:
+                assert torch.all(out[b, sl] == 0)
+                continue
+            logits = q[b, sl].double() @ k.T / math.sqrt(d)
+            # fp32 sums of at most 2^16 terms in splits of 320: a few 2^-24 of values of order 1
+            assert (out[b, sl].double() - torch.softmax(logits, 1) @ v).abs().max() <= 1e-5, (n_new, s)
+            assert (lse[b, sl].double() - torch.logsumexp(logits, 1)).abs().max() <= 1e-5, (n_new, s)
+
+
 @pytest.mark.parametrize("dtype,cap", [(torch.bfloat16, 300), (torch.float32, 20)])
 def test_decode_with_appended_rows(dtype, cap):
     """Generation after compression: each step appends one K/V row per KV head (sgdkv_append_kv)
