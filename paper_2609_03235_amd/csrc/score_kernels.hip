@@ -298,8 +298,9 @@ __global__ __launch_bounds__(kScoreBlock, 1) void colsum_kernel(CompressArgs a) 
 // x 4 x 8 heads of d 64 238 -> 207, 256K x 2 with a 32-token window 142 -> 121, 64K x 8 heads of d 64
 // with 128 rows 40 -> 32.
 constexpr int kKeyTurn = 64;  // keys of a wave's turn
-constexpr int kKeyChunkMin = 3584;      // keys of a workgroup from which the turns are worth it
-constexpr int kKeyChunkMinTall = 6144;  // the same for more than sixteen row blocks
+// keys of a workgroup from which the turns are worth it: up to sixteen row blocks; with up to 24 twice,
+// with more three times as many
+constexpr int kKeyChunkMin = 3584;
 
 template <typename T, int D>
 __global__ __launch_bounds__(kScoreBlock, 1) void colsum_keys_kernel(CompressArgs a) {
@@ -448,15 +449,17 @@ static hipError_t launch_colsum_t(const CompressArgs& a, hipStream_t st) {
     const dim3 cgrid(a.n_col_chunks, a.B * a.Hkv, a.n_rsplit);
     if constexpr (sizeof(T) == 2) {
       // The keys a workgroup has make the difference: short chunks lose to the last turns' spread and
-      // to filling the rows' LDS, the more rows the longer. Whole call, tiles / this: 128 rows at 2048
-      // keys 88.2 / 90.4 us, 4096 147.6 / 146.7, 8192 283.9 / 277.2, 256 rows at 2048 114.0 / 115.2, 3072 155.7 /
-      // 151.8, 16384 735 / 685; 448 rows at 4096 266.1 / 266.9, 6144 389.8 / 388.0, 16384 996 / 973, 49152
-      // 3071 / 2934; 512 rows at 6144 429.3 / 427.8, 8192 557 / 550, 16384 1103 / 1082 (1138 / 1116 on another
-      // card). A chunk holds no more keys than its segment: 256 sequences of 1024 keys, 256 rows, 312 / 332,
-      // 64 of 3072 161.7 / 157.9. Ipt. max loses to its reduction per head (100K x 1: 98 / 102 for the pass).
+      // to filling the rows' LDS, the more rows the longer, and the more so where pass 1 has not left the
+      // keys in the last-level cache (a given LSE). Whole call over inputs in turn, tiles / this: 128 rows at
+      // 2048 keys 88.2 / 90.4 us, 4096 161.7 / 157.4, 8192 294 / 282; 256 rows at 2048 114.0 / 115.2, 4096 212 /
+      // 204, 16384 741 / 694; 320 rows at 8192 444 / 426 (LSE given 259 / 250), 384 486 / 473 (275 / 275); 448
+      // rows at 4096 279.5 / 280.3, 8192 531 / 529 (298 / 301), 16384 1035 / 1010 (580 / 564); 512 rows at 8192 582 /
+      // 585 (325 / 330), 16384 1149 / 1128 (639 / 618). A chunk holds no more keys than its segment: 256 sequences
+      // of 1024 keys, 256 rows, 312 / 332, 64 of 3072 161.7 / 157.9. Ipt. max loses to its reduction per head
+      // (100K x 1: 98 / 102 for the pass).
       const int nrb = (a.rs_rows + 15) / 16;
       const int64_t keys = a.score_chunk < a.n_scored ? a.score_chunk : a.n_scored;
-      if (a.agg != 1 && keys >= (nrb <= 16 ? kKeyChunkMin : kKeyChunkMinTall)) {
+      if (a.agg != 1 && keys >= (nrb <= 16 ? kKeyChunkMin : nrb <= 24 ? 2 * kKeyChunkMin : 3 * kKeyChunkMin)) {
         SGDKV_LAUNCH("score_colsum", (colsum_keys_kernel<T, D>), cgrid, sblk, st, a);
         return hipGetLastError();
       }

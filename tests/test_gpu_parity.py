@@ -196,14 +196,16 @@ def test_pool_kernel_widths(kp):
 @pytest.mark.parametrize("B,C,Hq,Hkv,d,w,agg", [
     (18, 32768, 28, 4, 128, 16, sg.GROUP_MEAN), (32, 32801, 4, 2, 64, 8, sg.GROUP_IPT_MEAN),
     (9, 65100, 8, 8, 64, 17, sg.GROUP_MEAN), (2, 140000, 16, 2, 128, 64, sg.GROUP_IPT_ONLY),
-    (2, 131072, 28, 4, 128, 128, sg.GROUP_MEAN), (6, 140000, 16, 2, 128, 64, sg.GROUP_IPT_ONLY),
-    (4, 100001, 20, 4, 64, 100, sg.GROUP_IPT_MEAN), (4, 66000, 20, 4, 64, 128, sg.GROUP_IPT_ONLY),
-    (8, 50011, 16, 4, 64, 68, sg.GROUP_MEAN), (64, 3700, 8, 4, 64, 32, sg.GROUP_MEAN),
+    (2, 131072, 28, 4, 128, 128, sg.GROUP_MEAN), (10, 140000, 16, 2, 128, 64, sg.GROUP_IPT_ONLY),
+    (7, 100001, 20, 4, 64, 100, sg.GROUP_IPT_MEAN), (4, 66000, 20, 4, 64, 128, sg.GROUP_IPT_ONLY),
+    (11, 66000, 28, 2, 64, 64, sg.GROUP_IPT_MEAN),
+    (10, 50011, 16, 4, 64, 68, sg.GROUP_MEAN), (64, 3700, 8, 4, 64, 32, sg.GROUP_MEAN),
     (64, 3600, 8, 4, 64, 32, sg.GROUP_MEAN)])
 @pytest.mark.parametrize("given", [False, True])
 def test_scores_with_long_chunks(B, C, Hq, Hkv, d, w, agg, given):
-    """Pass 2 with the keys in registers (workgroups of 3584 keys and more, 6144 with more than sixteen
-    row blocks; 140000 x 2 and 3600 x 64 fall just short and take the tiles): one to 32 row blocks (odd
+    """Pass 2 with the keys in registers (workgroups of 3584 keys and more, twice as many with more than
+    sixteen row blocks, three times with more than 24; 140000 x 2, 131072 x 2 and 3600 x 64 fall short
+    and take the tiles): one to 32 row blocks (odd
     and even, part blocks, two row splits), last turns of part keys, with the window rows' LSE computed
     or given. Every sequence repeats the first one's tensors except the last, so the oracle runs on two
     of them; all of the others must match the first bit for bit (their chunks are handed out in another
