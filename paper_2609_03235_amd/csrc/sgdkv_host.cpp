@@ -404,13 +404,13 @@ sgdkv_status plan_compress(const sgdkv_compress_desc* d, int64_t win0, CompressP
   // pass 1 covers the keys some window row sees, [0, min(C, win0 + w)): the whole tiles every row
   // sees in uniform chunks (about one workgroup per CU), the rest (at most w + 127 keys) in short
   // tail chunks. Those get workgroups of their own (about 5 us each) where they run beside the
-  // uniform chunks, at most one workgroup per CU in all, for which a uniform chunk may be a tile
-  // longer; run after them they cost the launch those 5 us (5 % at 100K x 1). Otherwise workgroups of
-  // uniform chunks do them after their own keys, where a tail chunk takes about two thirds of a tile's
-  // time (2 of 3.2 us): the last one's alone if it is shorter than the rest by a tile for each of them
-  // (100K x 1: pass 1 84 us, 88 with one each on the last seven), else one each on the last chunks'
-  // (128K x 8: 409 us, 415 with all four on the last). The chunk sizes depend on C and w only, so the
-  // workspace does not depend on win0.
+  // uniform chunks, on CUs that those leave idle (one after the other, about three tiles' time each,
+  // while the uniform chunks last), for which a uniform chunk may be a tile longer; run after them
+  // they cost the launch those 5 us (5 % at 100K x 1). Otherwise workgroups of uniform chunks do them
+  // after their own keys, where a tail chunk takes about two thirds of a tile's time (2 of 3.2 us): the
+  // last one's alone if it is shorter than the rest by a tile for each of them (100K x 1: pass 1 84 us,
+  // 88 with one each on the last seven), else one each on the last chunks' (128K x 8: 409 us, 415 with all
+  // four on the last). The chunk sizes depend on C and w only, so the workspace does not depend on win0.
   {
     const int64_t vis_end = std::min<int64_t>(a.C, win0 + a.w);
     const int64_t open_end = std::min<int64_t>(a.C, win0);
@@ -423,18 +423,34 @@ sgdkv_status plan_compress(const sgdkv_compress_desc* d, int64_t win0, CompressP
                                1 << 16);
     };
     a.lse_chunk = chunk_for(sgdkv::kScoreWorkgroups);
+    // Rounding up the chunks of every segment can give more than one workgroup per CU (20 segments: 13
+    // chunks each, 260): the last, short chunks' workgroups then share the units that the full ones
+    // leave, in rounds (with about six tiles' time for their start and tail chunks), after those if
+    // they leave none. Where that takes longer than one chunk less per segment, that is planned instead
+    // (5 sequences of 40000 keys, four heads, 224 / 448 rows: pass 1 57 / 85 us, 84 / 126 otherwise).
+    const int64_t nsr = nseg * a.n_rsplit, units = sgdkv::kScoreWorkgroups;
+    const int64_t n1 = ceil_div(a.C, a.lse_chunk);
+    if (nsr <= units && nsr * n1 > units) {
+      const int64_t fewer = std::min<int64_t>(round_up(ceil_div(a.C, units / nsr), sgdkv::kScoreChunkQuantum), 1 << 16);
+      const int64_t left = units - nsr * (n1 - 1);
+      const int64_t last = ceil_div(a.C - (n1 - 1) * a.lse_chunk, sgdkv::kLseTile) + 6;
+      const int64_t rounds = left > 0 ? ceil_div(nsr, left) * last : a.lse_chunk / sgdkv::kLseTile + last;
+      if (fewer / sgdkv::kLseTile + 3 < rounds) a.lse_chunk = fewer;
+    }
     if (tails < sgdkv::kScoreWorkgroups) {
       const int64_t beside = chunk_for(sgdkv::kScoreWorkgroups - tails);
-      if (beside - a.lse_chunk <= sgdkv::kLseTile) a.lse_chunk = beside;
+      if (beside - a.lse_chunk <= sgdkv::kLseTile) a.lse_chunk = std::max(a.lse_chunk, beside);
     }
     a.lse_tail0 = open_end / sgdkv::kLseTile * sgdkv::kLseTile;
     a.n_lse_head = (int)ceil_div(a.lse_tail0, a.lse_chunk);
     a.n_lse_chunks = a.n_lse_head + (int)ceil_div(vis_end - a.lse_tail0, sgdkv::kLseTail);
-    const bool own = nseg * a.n_rsplit * a.n_lse_chunks <= sgdkv::kScoreWorkgroups || a.n_lse_head == 0;
+    const int n_tail_chunks = a.n_lse_chunks - a.n_lse_head;
+    const int64_t idle = units - nsr * a.n_lse_head;  // CUs beside the uniform chunks
+    const bool own = a.n_lse_head == 0 || nsr * n_tail_chunks <= idle ||
+                     (idle > 0 && ceil_div(nsr * n_tail_chunks, idle) * 3 <= a.lse_chunk / sgdkv::kLseTile);
     a.n_lse_wgs = own ? a.n_lse_chunks : a.n_lse_head;
-    const int n_tails = a.n_lse_chunks - a.n_lse_head;
     const int64_t spare = (a.n_lse_head * a.lse_chunk - a.lse_tail0) / sgdkv::kLseTile;  // tiles
-    a.lse_tailers = own ? 0 : spare >= n_tails ? 1 : std::min(n_tails, a.n_lse_head);
+    a.lse_tailers = own ? 0 : spare >= n_tail_chunks ? 1 : std::min(n_tail_chunks, a.n_lse_head);
     p.lse_chunks_max = (int)(ceil_div(a.C, a.lse_chunk) + tails_max);
   }
   a.n_col_chunks = (int)ceil_div(a.n_scored, a.score_chunk);

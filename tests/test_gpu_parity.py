@@ -269,11 +269,13 @@ def test_window_lse_tail_chunks(C, w, win0, dtype):
 
 @pytest.mark.parametrize("B,C,Hq,w,win0", [
     (32, 1024, 14, 64, None), (40, 700, 14, 64, None), (33, 1300, 14, 16, None), (32, 1024, 8, 64, 1024),
-    (20, 900, 18, 64, None), (100, 1500, 4, 128, 1111)])
+    (20, 900, 18, 64, None), (100, 1500, 4, 128, 1111), (10, 12507, 4, 32, None), (20, 12507, 14, 16, None)])
 def test_window_lse_tail_chunks_of_a_batch(B, C, Hq, w, win0):
     """Batches whose tail chunks of pass 1 have no workgroups of their own: one each on the last uniform
     chunks' workgroups, several each where the tails outnumber those, all on the last one where it is
-    short enough, none at all; with two row splits. Every sequence but the last repeats the first."""
+    short enough, none at all; with two row splits; batches whose segments get one chunk less than the
+    rounded-up share, with tail workgroups beside them or not. Every sequence but the last repeats the
+    first."""
     Hkv, d = 2, 64
     wl = workloads.Workload("tails", "tails", 1, Hq, Hkv, d, C, w, 5, 0, 0, 2, "bf16", 29, "beta")
     t = workloads.torch_layer_tensors(wl, 0, DEV)
