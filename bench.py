@@ -147,13 +147,14 @@ def parse():
 # ------------------------------------------------------------------ HBM traffic from counters
 # the library's name for each kernel -> a pattern of its (demangled) name in rocprofv3's output
 KERNEL_OF = {  # demangled ("sgdkv::name<...") or mangled ("_ZN5sgdkv<len>name...") in rocprofv3's output
-    "score_lse": r"sgdkv(::|\d+)lse_kernel", "score_colsum": r"sgdkv(::|\d+)colsum_kernel",
+    "score_lse": r"sgdkv(::|\d+)lse_kernel", "score_colsum": r"sgdkv(::|\d+)colsum_(keys_)?kernel",
     "lse_merge": r"sgdkv(::|\d+)lse_merge_kernel", "gather": r"sgdkv(::|\d+)copy_rows_kernel",
     "decode_split": r"sgdkv(::|\d+)decode_split_kernel", "decode_combine": r"sgdkv(::|\d+)decode_combine_kernel",
     "pool_radix_hist": r"sgdkv(::|\d+)radix_pass_kernel(<0, true, true|ILi0ELb1ELb1E)",
     "radix_hist": r"sgdkv(::|\d+)radix_pass_kernel(<[123], false, true|ILi[123]ELb0ELb1E)",
     "compact": r"sgdkv(::|\d+)compact_kernel"}
-SCORE_SOURCES = ("lse_pass.h", "lse_kernels.hip", "lse_kernels_ilp.hip", "score_kernels.hip", "score_common.h")
+SCORE_SOURCES = ("lse_pass.h", "lse_kernels.hip", "lse_kernels_ilp.hip", "colsum_pass.h", "score_kernels.hip",
+                 "score_kernels_ilp.hip", "score_common.h")
 SOURCE_OF = {"score_lse": SCORE_SOURCES, "score_colsum": SCORE_SOURCES, "lse_merge": SCORE_SOURCES,
              "gather": ("select_kernels.hip",), "pool_radix_hist": ("select_kernels.hip",),
              "radix_hist": ("select_kernels.hip",), "compact": ("select_kernels.hip",),

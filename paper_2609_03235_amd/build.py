@@ -22,11 +22,12 @@ HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = "gfx950"
 COMMON = ["-O3", "-std=c++17", "-fPIC", "-I", INCLUDE, "-I", CSRC, "-Wall", "-Wno-unused-command-line-argument"]
 DEVICE = [f"--offload-arch={ARCH}", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
-# The scheduler that puts instruction parallelism first, for the pass-1 instances that measured faster
-# with it (lse_pass.h); pass 2 measured slower with it (128K x 8: 435 us against 428).
-FILE_FLAGS = {"lse_kernels_ilp.hip": ["-mllvm", "-amdgpu-sched-strategy=max-ilp"]}
-KERNEL_SOURCES = ["lse_kernels.hip", "lse_kernels_ilp.hip", "score_kernels.hip", "select_kernels.hip",
-                  "decode_kernels.hip", "decode_scratch.hip"]
+# The scheduler that puts instruction parallelism first, for the instances of the score passes that
+# measured faster with it (lse_pass.h, colsum_pass.h).
+ILP = ["-mllvm", "-amdgpu-sched-strategy=max-ilp"]
+FILE_FLAGS = {"lse_kernels_ilp.hip": ILP, "score_kernels_ilp.hip": ILP}
+KERNEL_SOURCES = ["lse_kernels.hip", "lse_kernels_ilp.hip", "score_kernels.hip", "score_kernels_ilp.hip",
+                  "select_kernels.hip", "decode_kernels.hip", "decode_scratch.hip"]
 HOST_SOURCES = ["sgdkv_host.cpp", "profile.cpp"]
 
 

@@ -247,6 +247,25 @@ def test_every_instance_of_pass_one(G, w, d, dtype):
     _check_kept(res, orc, t["q_win"].shape, C, w, 0, w, budgets, "pass 1", rtol=_score_rtol(t["q_win"]))
 
 
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("agg", [sg.GROUP_MEAN, sg.GROUP_IPT_MAX])
+@pytest.mark.parametrize("G,w", [(2, 64), (4, 64), (5, 48), (6, 64), (8, 48), (8, 64), (6, 80)])
+def test_every_instance_of_pass_two(G, w, agg, d, dtype):
+    """The tile kernel with one to four row blocks per wave, with Ipt. max in head-aligned waves and not:
+    each instance is compiled in one of two files, whose rule the launch shares."""
+    B, Hkv, C = 2, 2, 2100
+    wl = workloads.Workload("colsum", "colsum", 1, G * Hkv, Hkv, d, C, w, 5, 0, 0, B, "bf16", 43, "beta")
+    t = workloads.torch_layer_tensors(wl, 0, DEV, dtype=dtype)
+    sig = np.random.Generator(np.random.PCG64(G + w)).uniform(0.1, 1.0, size=G * Hkv)
+    budgets = np.array([w + C // 3, C // 2])
+    _announce(f"pass 2 G={G} w={w} agg={agg} d={d} {dtype}")
+    res, orc = _compress_both(t["q_win"], t["k"], t["v"], budgets, kp=5, s=0, W=w, agg=agg,
+                              qhead_scores=sig if agg else None)
+    _check_scores(res["scores"].cpu().numpy(), orc["pooled"], "pass 2", rtol=_score_rtol(t["q_win"]))
+    _check_kept(res, orc, t["q_win"].shape, C, w, 0, w, budgets, "pass 2", rtol=_score_rtol(t["q_win"]))
+
+
 @pytest.mark.parametrize("C,w,win0,dtype", [
     (640, 64, None, torch.bfloat16), (641, 64, 577, torch.bfloat16), (703, 63, None, torch.bfloat16),
     (767, 64, 640, torch.bfloat16), (900, 33, 900, torch.bfloat16), (1024, 16, 1024, torch.float32),
