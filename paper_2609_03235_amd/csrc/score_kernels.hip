@@ -54,6 +54,7 @@ constexpr int kKeyTurn = 64;  // keys of a wave's turn
 // keys of a workgroup from which the turns are worth it: up to sixteen row blocks; with up to 24 twice,
 // with more three times as many
 constexpr int kKeyChunkMin = 3584;
+constexpr int kKeyChunkMinFlat = 32768;  // with up to four of d 128
 
 template <typename T, int D>
 __global__ __launch_bounds__(kScoreBlock, 1) void colsum_keys_kernel(CompressArgs a) {
@@ -203,12 +204,15 @@ static bool colsum_by_keys(const CompressArgs& a) {
   // 204, 16384 741 / 694; 320 rows at 8192 444 / 426 (LSE given 259 / 250), 384 486 / 473 (275 / 275); 448
   // rows at 4096 279.5 / 280.3, 8192 531 / 529 (298 / 301), 16384 1035 / 1010 (580 / 564); 512 rows at 8192 582 /
   // 585 (325 / 330), 16384 1149 / 1128 (639 / 618). A chunk holds no more keys than its segment: 256 sequences
-  // of 1024 keys, 256 rows, 312 / 332, 64 of 3072 161.7 / 157.9. Ipt. max loses to its reduction per head
-  // (100K x 1: 98 / 102 for the pass).
+  // of 1024 keys, 256 rows, 312 / 332, 64 of 3072 161.7 / 157.9. Up to four row blocks of d 128 leave the pass to
+  // the memory, which whole tiles read better, except in the longest chunks (64 rows at 4096 keys 138 / 145,
+  // 8192 261 / 269, 16384 521 / 522, 65536 2017 / 2004; d 64 at 8192 166 / 155). Ipt. max loses to its reduction per
+  // head (100K x 1: 98 / 102 for the pass).
   const int nrb = (a.rs_rows + 15) / 16;
   const int64_t keys = a.score_chunk < a.n_scored ? a.score_chunk : a.n_scored;
-  return a.dtype == 1 && a.agg != 1 &&
-         keys >= (nrb <= 16 ? kKeyChunkMin : nrb <= 24 ? 2 * kKeyChunkMin : 3 * kKeyChunkMin);
+  if (a.dtype != 1 || a.agg == 1) return false;
+  if (a.D == 128 && nrb <= 4) return keys >= kKeyChunkMinFlat;
+  return keys >= (nrb <= 16 ? kKeyChunkMin : nrb <= 24 ? 2 * kKeyChunkMin : 3 * kKeyChunkMin);
 }
 
 hipError_t launch_scores(const CompressArgs& a, hipStream_t st) {

@@ -200,12 +200,13 @@ def test_pool_kernel_widths(kp):
     (7, 100001, 20, 4, 64, 100, sg.GROUP_IPT_MEAN), (4, 66000, 20, 4, 64, 128, sg.GROUP_IPT_ONLY),
     (11, 66000, 28, 2, 64, 64, sg.GROUP_IPT_MEAN),
     (10, 50011, 16, 4, 64, 68, sg.GROUP_MEAN), (64, 3700, 8, 4, 64, 32, sg.GROUP_MEAN),
-    (64, 3600, 8, 4, 64, 32, sg.GROUP_MEAN)])
+    (64, 3600, 8, 4, 64, 32, sg.GROUP_MEAN), (9, 65100, 8, 8, 128, 17, sg.GROUP_MEAN),
+    (33, 262200, 1, 1, 128, 24, sg.GROUP_MEAN)])
 @pytest.mark.parametrize("given", [False, True])
 def test_scores_with_long_chunks(B, C, Hq, Hkv, d, w, agg, given):
     """Pass 2 with the keys in registers (workgroups of 3584 keys and more, twice as many with more than
-    sixteen row blocks, three times with more than 24; 140000 x 2, 131072 x 2 and 3600 x 64 fall short
-    and take the tiles): one to 32 row blocks (odd
+    sixteen row blocks, three times with more than 24, 32768 with up to four of d 128; 140000 x 2, 131072 x 2, 3600 x
+    64 and 65100 x 9 of d 128 fall short and take the tiles): one to 32 row blocks (odd
     and even, part blocks, two row splits), last turns of part keys, with the window rows' LSE computed
     or given. Every sequence repeats the first one's tensors except the last, so the oracle runs on two
     of them; all of the others must match the first bit for bit (their chunks are handed out in another
