@@ -889,8 +889,8 @@ sgdkv_status plan_decode(const sgdkv_decode_desc* d, const int64_t* offsets_host
   // token like the next ones. With appended rows every segment launches workgroups for them, which
   // count (44 segments, 170K rows and 33 appended ones each: 27.7 us, without counting them 37.6, before 31.7).
   // If no split length of up to 320 rows fits them, shorter splits in more workgroups are the faster: 64
-  // rows where 128 would leave units idle, else 128; 64 also where those alone fit (128 segments of 470
-  // rows: 25.3 us, 26.6 with 128 rows).
+  // rows where 128 would leave units idle, else 128; past 32 segments 64 also where those alone fit (128
+  // segments of 470 rows: 25.3 us, 26.6 with 128 rows).
   // A cache that launches more than two rounds gets splits twice as long (fewer workgroups, each with
   // less of its fixed cost per row, and fewer partials to combine: decode per 128K x B 8 layer -3.7 %;
   // the 256K x B 16 and 1M x B 32 caches already have splits of 512 rows and more)
@@ -925,7 +925,7 @@ sgdkv_status plan_decode(const sgdkv_decode_desc* d, const int64_t* offsets_host
         }
       }
       one = n <= 0 || fewest + nseg * appended_wgs(n, kDecodeUnitChunk) <= kUnits;
-      if (n > 0 && workgroups(kDecodeMinChunk / 2) <= kUnits)
+      if (n > 0 && nseg > kUnits - room && workgroups(kDecodeMinChunk / 2) <= kUnits)
         a.chunk = kDecodeMinChunk / 2, one = true;  // (appended rows beside such short ones cost little)
       else if (one)
         a.chunk = n <= 0 ? one_round(room, 0) : one_round(kUnits, n);

@@ -523,7 +523,8 @@ def test_decode_split_length_of_small_caches(lens):
 @pytest.mark.parametrize("lens", SMALL_CACHES + [[2650] * 64, [5650] * 44, [3600] * 64, [470] * 128, [300] * 200])
 @pytest.mark.parametrize("cap", [1, 64, 300, 3000])
 def test_decode_workspace_of_small_caches_covers_every_appended_count(lens, cap):
-    """With appended rows the splits are of 64 rows if those alone launch one round, else the shortest that
+    """With appended rows the splits of more than 32 segments are of 64 rows if those alone launch one
+    round, else the shortest that
     do with the workgroups of the appended rows, else 64 rows where 128 would leave units idle, else 128: the workspace of a capacity holds the
     slots of every count of appended rows up to it, and of the plan without any."""
     G, d, n = 7, 128, len(lens)
@@ -534,7 +535,7 @@ def test_decode_workspace_of_small_caches_covers_every_appended_count(lens, cap)
     slots = sg.decode_workspace_size(desc, oh, cap) // (G * (d + 2) * 4)
     assert slots >= sg.decode_workspace_size(desc, oh) // (G * (d + 2) * 4)
     for n_new in sorted({1, 33, 64, cap // 2, cap} & set(range(1, cap + 1))):
-        c = (64 if wgs(64) <= 256 else _small_cache_splits(lens, n_new)) if plain else None
+        c = (64 if n > 32 and wgs(64) <= 256 else _small_cache_splits(lens, n_new)) if plain else None
         if c is None:
             c = (64 if wgs(128) < 256 else 128) if plain else 256 if wgs(128) > 1024 else 128
         if wgs(c) <= 512:
