@@ -152,12 +152,13 @@ KERNEL_OF = {  # demangled ("sgdkv::name<...") or mangled ("_ZN5sgdkv<len>name..
     "decode_split": r"sgdkv(::|\d+)decode_split_kernel", "decode_combine": r"sgdkv(::|\d+)decode_combine_kernel",
     "pool_radix_hist": r"sgdkv(::|\d+)radix_pass_kernel(<0, true, true|ILi0ELb1ELb1E)",
     "radix_hist": r"sgdkv(::|\d+)radix_pass_kernel(<[123], false, true|ILi[123]ELb0ELb1E)",
-    "compact": r"sgdkv(::|\d+)compact_kernel"}
+    "compact": r"sgdkv(::|\d+)compact_kernel", "select_segment": r"sgdkv(::|\d+)select_segment_kernel"}
 SCORE_SOURCES = ("lse_pass.h", "lse_kernels.hip", "lse_kernels_ilp.hip", "colsum_pass.h", "score_kernels.hip",
                  "score_kernels_ilp.hip", "score_common.h")
 SOURCE_OF = {"score_lse": SCORE_SOURCES, "score_colsum": SCORE_SOURCES, "lse_merge": SCORE_SOURCES,
              "gather": ("select_kernels.hip",), "pool_radix_hist": ("select_kernels.hip",),
              "radix_hist": ("select_kernels.hip",), "compact": ("select_kernels.hip",),
+             "select_segment": ("select_kernels.hip",),
              "decode_split": ("decode_kernels.hip",), "decode_combine": ("decode_kernels.hip",)}
 SHARED_SOURCES = ("device_common.h", "mfma_frag.h", "sgdkv_internal.h", "segment_init.h")
 
