@@ -256,7 +256,7 @@ __global__ __launch_bounds__(kScoreBlock, 1) void colsum_kernel(CompressArgs a) 
 
 // Instances compiled with the scheduler that puts instruction parallelism first: bf16 keys at d = 64
 // with sums over all rows and one, two or four row blocks per wave, with Ipt. max one or four; at d = 128 Ipt. max
-// with three. Pass 2 with it / without, four heads: d 64, 8 x 13601 keys of 8 heads, 32 rows 23.8 / 24.7 us, 32K x 2,
+// with three. Pass 2 with it / without, four heads: d 64, 13601 x 5 of 8 heads, 32 rows 23.8 / 24.7 us, 32K x 2,
 // 256 rows 18.8 / 19.4, 448 26.3 / 27.1, 384 24.6 / 24.2; Ipt. max, 32K x 8, 32 rows 35.0 / 36.9, 128 47.7 / 49.0, 192 60.2 /
 // 58.6, 384 110.8 / 110.5, 512 101.3 / 102.7; d 128 Ipt. max 128 rows 70.9 / 68.1, 256 90.0 / 86.9, 384 135.5 / 139.0,
 // 448 124.7 / 127.2 (but 100K x 1 of 896 rows 96.8 / 95.6), sums over all rows 448 rows 35.7 / 35.2 (128K x 8 435 /

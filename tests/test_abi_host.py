@@ -524,9 +524,9 @@ def test_decode_split_length_of_small_caches(lens):
 @pytest.mark.parametrize("cap", [1, 64, 300, 3000])
 def test_decode_workspace_of_small_caches_covers_every_appended_count(lens, cap):
     """With appended rows the splits of more than 32 segments are of 64 rows if those alone launch one
-    round, else the shortest that
-    do with the workgroups of the appended rows, else 64 rows where 128 would leave units idle, else 128: the workspace of a capacity holds the
-    slots of every count of appended rows up to it, and of the plan without any."""
+    round, else the shortest that do with the workgroups of the appended rows, else 64 rows where 128
+    would leave units idle, else 128: the workspace of a capacity holds the slots of every count of
+    appended rows up to it, and of the plan without any."""
     G, d, n = 7, 128, len(lens)
     desc = sg.DecodeDesc(1, n * G, n, d, sg.DTYPE_BF16, sg.DTYPE_F32, 0.0)
     oh = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
