@@ -43,20 +43,30 @@ __device__ __forceinline__ int64_t uniform64(int64_t v) {
 // A decode workgroup's segment and its index in the segment's workgroup layout (x < n_cwg: its
 // compressed rows; n_cwg + j: its appended rows), and how many workgroups were launched for the
 // segment's compressed rows (ncw): from the compact table, or the (x, segment) grid.
+// On the compact grid the workgroups of the compressed rows come first, segment by segment, then those
+// of the appended rows, which are shorter: launched among the others they put two long workgroups on
+// some compute units and short ones on the next (384 segments, 420K rows and 67 appended each, fp32 of
+// d 64: split kernel 79 us, 111 so; 96 segments, 200K rows, bf16 of d 128 26.8, 41.5 so).
 __device__ __forceinline__ void decode_workgroup(const DecodeArgs& a, int& seg, int& x, int& ncw) {
   if (a.compact) {
-    const int flat = blockIdx.x;
-    // the last segment that starts at or before the workgroup: each wave looks at 64 segments of
-    // the table at once (a binary search is a chain of scalar loads, one per halving)
     const int nseg = a.B * a.Hkv, lane = threadIdx.x & 63;
-    int upto = 0;
+    const int flat = blockIdx.x, late = flat - a.n_first_new;
+    if (late < 0) {
+      // the last segment whose compressed rows' workgroups start at or before this one: each wave looks
+      // at 64 segments of the table at once (a binary search is a chain of scalar loads, one per halving)
+      int upto = 0;
 #pragma unroll 1
-    for (int i = 0; i < nseg; i += 64)
-      upto += __popcll(__ballot(i + lane < nseg && a.wg_start[i + lane < nseg ? i + lane : 0] <= flat));
-    seg = upto - 1;
+      for (int i = 0; i < nseg; i += 64) {
+        const int at = i + lane < nseg ? i + lane : 0;
+        upto += __popcll(__ballot(i + lane < nseg && a.wg_start[at] - at * a.n_new_wg <= flat));
+      }
+      seg = upto - 1;
+      x = flat - (a.wg_start[seg] - seg * a.n_new_wg);
+    } else {
+      seg = late / a.n_new_wg;
+      x = a.n_cwg + late % a.n_new_wg;
+    }
     ncw = a.wg_start[seg + 1] - a.wg_start[seg] - a.n_new_wg;
-    const int local = flat - a.wg_start[seg];
-    x = local < ncw ? local : a.n_cwg + (local - ncw);
   } else {
     seg = blockIdx.y;
     x = blockIdx.x;
@@ -397,7 +407,7 @@ __global__ __launch_bounds__(kDecodeBlock, OCC) void decode_split_kernel(DecodeA
   int64_t sbase;
   int nsl;
   segment_slots(a, seg, sbase, nsl);
-  const int64_t slot = a.compact ? (int64_t)blockIdx.x - sbase : x;  // within the segment's slots
+  const int64_t slot = a.compact && appended ? ncw + wg : x;  // within the segment's slots
   const rsrc_t mr = make_rsrc(a.part_ms + sbase * G * 2, (uint64_t)nsl * G * 8);
   const rsrc_t orr = make_rsrc(a.part + sbase * G * D, (uint64_t)nsl * G * D * 4);
   for (int idx = tid; idx < G * (D / 4); idx += kDecodeBlock) {  // four columns per thread

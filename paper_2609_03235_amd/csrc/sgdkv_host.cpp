@@ -1040,6 +1040,7 @@ sgdkv_status decode_step(const sgdkv_decode_desc* desc, const void* q, const voi
       run += wgs[(size_t)i] + a.n_new_wg;
       a.wg_start[i + 1] = (int32_t)run;
     }
+    a.n_first_new = (int)(run - nseg * a.n_new_wg);
   }
   a.part = static_cast<float*>(workspace);
   a.part_ms = a.part + (size_t)a.n_slots * a.G * a.D;

@@ -147,12 +147,14 @@ struct DecodeArgs {
   int64_t cap, n_new;
   int n_new_chunks;   // ceil(n_new / chunk)
   int64_t n_slots;    // slots the workspace holds (planned for the appended region's capacity)
-  // Compact grid (B*Hkv <= kMaxCompactSegs): only workgroups with work are launched, segment
-  // after segment (from the host copy of the offsets); segment s owns workgroups
-  // [wg_start[s], wg_start[s+1]), its compressed rows' first, then n_new_wg for its appended rows.
+  // Compact grid (B*Hkv <= kMaxCompactSegs): only workgroups with work are launched, those of the
+  // compressed rows first, segment after segment (from the host copy of the offsets), then those of the
+  // appended rows. Segment s owns the slots [wg_start[s], wg_start[s+1]): its compressed rows', then
+  // n_new_wg for its appended rows.
   // Otherwise (compact = 0) the grid is (n_cwg + n_new_wg) x segments.
   int compact;
   int n_new_wg;       // ceil(n_new_chunks / waves per workgroup)
+  int n_first_new;    // compact grid: the first workgroup of appended rows
   int32_t wg_start[kMaxCompactSegs + 1];
 };
 
