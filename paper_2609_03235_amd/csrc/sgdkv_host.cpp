@@ -806,7 +806,8 @@ sgdkv_status plan_decode(const sgdkv_decode_desc* d, const int64_t* offsets_host
   const int64_t nseg = (int64_t)d->batch * d->num_kv_heads;
   if (nseg > 65535) return fail(SGDKV_ERR_UNSUPPORTED, "batch * num_kv_heads = %lld > 65535", (long long)nseg);
   if ((int64_t)d->batch * d->num_q_heads > 0x7FFFFFFFll) return fail(SGDKV_ERR_UNSUPPORTED, "batch * num_q_heads");
-  const int64_t rb = (int64_t)d->head_dim * (d->kv_dtype == 1 ? 2 : 4);
+  const int64_t rb_elt = d->kv_dtype == 1 ? 2 : 4;
+  const int64_t rb = (int64_t)d->head_dim * rb_elt;
   if (offsets_host[0] < 0) return fail(SGDKV_ERR_INVALID_ARG, "offsets[0] < 0");
   int64_t longest = 0, filled = 0;  // filled: segments with rows
   for (int64_t i = 0; i < nseg; ++i) {
@@ -887,10 +888,13 @@ sgdkv_status plan_decode(const sgdkv_decode_desc* d, const int64_t* offsets_host
   // Without appended rows the splits do not depend on the capacity; room is left for one workgroup
   // of appended rows per segment, up to 32, so that batches of up to 32 segments decode their first
   // token like the next ones. With appended rows every segment launches workgroups for them, which
-  // count (44 segments, 170K rows and 33 appended ones each: 27.7 us, without counting them 37.6, before 31.7).
-  // If no split length of up to 320 rows fits them, shorter splits in more workgroups are the faster: 64
-  // rows where 128 would leave units idle, else 128; past 32 segments 64 also where those alone fit (128
-  // segments of 470 rows: 25.3 us, 26.6 with 128 rows).
+  // count (44 segments, 170K rows and 33 appended ones each: 27.7 us, without counting them 37.6, before
+  // 31.7).
+  // Past 32 segments, where they take many of the units, the rows of such splits are set against those
+  // that a unit gets in the plan without this: splits of 64 rows where 128 would leave units idle, else
+  // of 128, so many per unit, each with a fixed cost of about 48 rows of bf16 or 16 of fp32 (80 segments,
+  // 90K rows, G 8, 160 rows in one round / 64 in two: bf16 26.5 / 26.4 us, fp32 57.0 / 47.8; 128 of 470 rows, 128
+  // / 64 26.6 / 25.3).
   // A cache that launches more than two rounds gets splits twice as long (fewer workgroups, each with
   // less of its fixed cost per row, and fewer partials to combine: decode per 128K x B 8 layer -3.7 %;
   // the 256K x B 16 and 1M x B 32 caches already have splits of 512 rows and more)
@@ -924,13 +928,25 @@ sgdkv_status plan_decode(const sgdkv_decode_desc* d, const int64_t* offsets_host
           n = std::min(n_new, capacity);
         }
       }
-      one = n <= 0 || fewest + nseg * appended_wgs(n, kDecodeUnitChunk) <= kUnits;
-      if (n > 0 && nseg > kUnits - room && workgroups(kDecodeMinChunk / 2) <= kUnits)
-        a.chunk = kDecodeMinChunk / 2, one = true;  // (appended rows beside such short ones cost little)
-      else if (one)
-        a.chunk = n <= 0 ? one_round(room, 0) : one_round(kUnits, n);
-      else if (workgroups(kDecodeMinChunk) < kUnits)
-        a.chunk = kDecodeMinChunk / 2;
+      if (n <= 0) {
+        one = true;
+        a.chunk = one_round(room, 0);
+      } else if (nseg <= kUnits - room && fewest + nseg * appended_wgs(n, kDecodeUnitChunk) <= kUnits) {
+        one = true;  // the room above
+        a.chunk = one_round(kUnits, n);
+      } else {
+        if (workgroups(kDecodeMinChunk) < kUnits) a.chunk = kDecodeMinChunk / 2;
+        const int64_t wgs = workgroups(a.chunk);
+        one = wgs <= kUnits;
+        if (fewest + nseg * appended_wgs(n, kDecodeUnitChunk) <= kUnits && !(one && a.chunk < kDecodeMinChunk)) {
+          const int64_t rounds = ceil_div(wgs + nseg * appended_wgs(n, a.chunk), kUnits);
+          const int64_t c = one_round(kUnits, n);
+          if (c <= rounds * a.chunk + (rounds - 1) * (rb_elt == 2 ? 48 : 16)) {
+            one = true;
+            a.chunk = c;
+          }
+        }
+      }
     } else if (workgroups(a.chunk) > 2 * kDecodeResident) {
       a.chunk = kDecodeMinChunk * 2;
     }

@@ -498,13 +498,12 @@ SMALL_CACHES = [[143000 // 32] * 32, [20000, 0, 17, 60000], [1] * 224, [1] * 225
                 [3000, 40] * 40, [0, 300000], [286720 // 4] * 4, [64] * 512]
 
 
-def _small_cache_splits(lens, n_new):
-    """The split length of a small cache: the shortest of 64 to 320 rows, in steps of 16, that launches at
-    most a workgroup (four splits) per compute unit, with those of the appended rows (without any, room
-    for one per segment, up to 32); None if there is none."""
-    n = len(lens)
-    units, per = (256, lambda c: -(-n_new // (4 * c))) if n_new else (256 - min(n, 32), lambda c: 0)
-    fits = [c for c in range(64, 321, 16) if sum(-(-l // (4 * c)) for l in lens) + n * per(c) <= units]
+def _small_cache_splits(lens):
+    """The split length of a small cache without appended rows: the shortest of 64 to 320 rows, in steps of
+    16, that launches at most a workgroup (four splits) per compute unit with room for one of appended
+    rows per segment, up to 32; None if there is none."""
+    units = 256 - min(len(lens), 32)
+    fits = [c for c in range(64, 321, 16) if sum(-(-l // (4 * c)) for l in lens) <= units]
     return fits[0] if fits else None
 
 
@@ -515,7 +514,7 @@ def test_decode_split_length_of_small_caches(lens):
     desc = sg.DecodeDesc(1, n * G, n, d, sg.DTYPE_BF16, sg.DTYPE_F32, 0.0)
     oh = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
     wgs = lambda c: int(sum(-(-l // (4 * c)) for l in lens))
-    chunk = _small_cache_splits(lens, 0) or (256 if wgs(128) > 1024 else 128)
+    chunk = _small_cache_splits(lens) or (256 if wgs(128) > 1024 else 128)
     if wgs(chunk) <= 512:  # past one round the workgroups are shared out over whole rounds
         assert sg.decode_workspace_size(desc, oh) == -(-wgs(chunk) * G * (d + 2) * 4 // 256) * 256
 
@@ -523,23 +522,20 @@ def test_decode_split_length_of_small_caches(lens):
 @pytest.mark.parametrize("lens", SMALL_CACHES + [[2650] * 64, [5650] * 44, [3600] * 64, [470] * 128, [300] * 200])
 @pytest.mark.parametrize("cap", [1, 64, 300, 3000])
 def test_decode_workspace_of_small_caches_covers_every_appended_count(lens, cap):
-    """With appended rows the splits of more than 32 segments are of 64 rows if those alone launch one
-    round, else the shortest that do with the workgroups of the appended rows, else 64 rows where 128
-    would leave units idle, else 128: the workspace of a capacity holds the slots of every count of
-    appended rows up to it, and of the plan without any."""
+    """With appended rows the split length of a small cache depends on their number: whatever it is, the
+    workspace of a capacity holds the slots of one workgroup per four splits and of the appended rows',
+    and those of the plan without any."""
     G, d, n = 7, 128, len(lens)
     desc = sg.DecodeDesc(1, n * G, n, d, sg.DTYPE_BF16, sg.DTYPE_F32, 0.0)
     oh = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
     wgs = lambda c: int(sum(-(-l // (4 * c)) for l in lens))
-    plain = _small_cache_splits(lens, 0)
     slots = sg.decode_workspace_size(desc, oh, cap) // (G * (d + 2) * 4)
     assert slots >= sg.decode_workspace_size(desc, oh) // (G * (d + 2) * 4)
+    chunks = range(64, 321, 16) if _small_cache_splits(lens) else [256 if wgs(128) > 1024 else 128]
     for n_new in sorted({1, 33, 64, cap // 2, cap} & set(range(1, cap + 1))):
-        c = (64 if n > 32 and wgs(64) <= 256 else _small_cache_splits(lens, n_new)) if plain else None
-        if c is None:
-            c = (64 if wgs(128) < 256 else 128) if plain else 256 if wgs(128) > 1024 else 128
-        if wgs(c) <= 512:
-            assert slots >= wgs(c) + n * -(-n_new // (4 * c)), (n_new, c)
+        for c in chunks:
+            if wgs(c) <= 512:
+                assert slots >= wgs(c) + n * -(-n_new // (4 * c)), (n_new, c)
 
 
 def test_decode_workspace_with_appended_rows():
