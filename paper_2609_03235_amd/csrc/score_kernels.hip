@@ -54,7 +54,7 @@ constexpr int kKeyTurn = 64;  // keys of a wave's turn
 // keys of a workgroup from which the turns are worth it: up to sixteen row blocks; with up to 24 twice,
 // with more three times as many
 constexpr int kKeyChunkMin = 3584;
-constexpr int kKeyChunkMinFlat = 32768;  // with up to four of d 128
+constexpr int kKeyChunkMinFlat = 32768;  // with up to four of d 128 and no LSE given
 
 template <typename T, int D>
 __global__ __launch_bounds__(kScoreBlock, 1) void colsum_keys_kernel(CompressArgs a) {
@@ -206,12 +206,13 @@ static bool colsum_by_keys(const CompressArgs& a) {
   // 585 (325 / 330), 16384 1149 / 1128 (639 / 618). A chunk holds no more keys than its segment: 256 sequences
   // of 1024 keys, 256 rows, 312 / 332, 64 of 3072 161.7 / 157.9. Up to four row blocks of d 128 leave the pass to
   // the memory, which whole tiles read better, except in the longest chunks (64 rows at 4096 keys 138 / 145,
-  // 8192 261 / 269, 16384 521 / 522, 65536 2017 / 2004; d 64 at 8192 166 / 155). Ipt. max loses to its reduction per
+  // 8192 261 / 269, 16384 521 / 522, 65536 2017 / 2004; LSE given at 8192 241 / 243, 12288 369 / 365; d 64 at
+  // 8192 166 / 155). Ipt. max loses to its reduction per
   // head (100K x 1: 98 / 102 for the pass).
   const int nrb = (a.rs_rows + 15) / 16;
   const int64_t keys = a.score_chunk < a.n_scored ? a.score_chunk : a.n_scored;
   if (a.dtype != 1 || a.agg == 1) return false;
-  if (a.D == 128 && nrb <= 4) return keys >= kKeyChunkMinFlat;
+  if (a.D == 128 && nrb <= 4) return keys >= (a.window_lse ? 3 * kKeyChunkMin : kKeyChunkMinFlat);
   return keys >= (nrb <= 16 ? kKeyChunkMin : nrb <= 24 ? 2 * kKeyChunkMin : 3 * kKeyChunkMin);
 }
 
