@@ -403,14 +403,16 @@ sgdkv_status plan_compress(const sgdkv_compress_desc* d, int64_t win0, CompressP
       1 << 16);
   // pass 1 covers the keys some window row sees, [0, min(C, win0 + w)): the whole tiles every row
   // sees in uniform chunks (about one workgroup per CU), the rest (at most w + 127 keys) in short
-  // tail chunks. Those get workgroups of their own (about 5 us each) where they run beside the
-  // uniform chunks, on CUs that those leave idle (one after the other, about three tiles' time each,
-  // while the uniform chunks last), for which a uniform chunk may be a tile longer; run after them
-  // they cost the launch those 5 us (5 % at 100K x 1). Otherwise workgroups of uniform chunks do them
-  // after their own keys, where a tail chunk takes about two thirds of a tile's time (2 of 3.2 us): the
-  // last one's alone if it is shorter than the rest by a tile for each of them (100K x 1: pass 1 84 us,
-  // 88 with one each on the last seven), else one each on the last chunks' (128K x 8: 409 us, 415 with all
-  // four on the last). The chunk sizes depend on C and w only, so the workspace does not depend on win0.
+  // tail chunks. Those get workgroups of their own (about 5 us each) where each finds an idle CU beside
+  // the uniform chunks, for which a uniform chunk may be a tile longer; run after them they cost the
+  // launch those 5 us (5 % at 100K x 1). Otherwise workgroups of uniform chunks do them after their own
+  // keys, where a tail chunk takes about two thirds of a tile's time (2 of 3.2 us): the last one's alone
+  // if it is shorter than the rest by a tile for each of them (100K x 1: pass 1 84 us, 88 with one each on
+  // the last seven), else one each on the last chunks' (128K x 8: 409 us, 415 with all four on the
+  // last). Before that, they may run on the idle CUs one after the other (about three tiles' time each)
+  // while the uniform chunks last, if every XCD has one: workgroups go to the XCDs in turn, whether these have
+  // room or not (150001 keys x 3 x 2 heads, four idle CUs: pass 1 112.8 us for 106.1 so). The chunk sizes depend
+  // on C and w only, so the workspace does not depend on win0.
   {
     const int64_t vis_end = std::min<int64_t>(a.C, win0 + a.w);
     const int64_t open_end = std::min<int64_t>(a.C, win0);
@@ -445,11 +447,12 @@ sgdkv_status plan_compress(const sgdkv_compress_desc* d, int64_t win0, CompressP
     a.n_lse_head = (int)ceil_div(a.lse_tail0, a.lse_chunk);
     a.n_lse_chunks = a.n_lse_head + (int)ceil_div(vis_end - a.lse_tail0, sgdkv::kLseTail);
     const int n_tail_chunks = a.n_lse_chunks - a.n_lse_head;
+    const int64_t spare = (a.n_lse_head * a.lse_chunk - a.lse_tail0) / sgdkv::kLseTile;  // tiles
     const int64_t idle = units - nsr * a.n_lse_head;  // CUs beside the uniform chunks
     const bool own = a.n_lse_head == 0 || nsr * n_tail_chunks <= idle ||
-                     (idle > 0 && ceil_div(nsr * n_tail_chunks, idle) * 3 <= a.lse_chunk / sgdkv::kLseTile);
+                     (spare < n_tail_chunks && idle >= 8 &&
+                      ceil_div(nsr * n_tail_chunks, idle) * 3 <= a.lse_chunk / sgdkv::kLseTile);
     a.n_lse_wgs = own ? a.n_lse_chunks : a.n_lse_head;
-    const int64_t spare = (a.n_lse_head * a.lse_chunk - a.lse_tail0) / sgdkv::kLseTile;  // tiles
     a.lse_tailers = own ? 0 : spare >= n_tail_chunks ? 1 : std::min(n_tail_chunks, a.n_lse_head);
     p.lse_chunks_max = (int)(ceil_div(a.C, a.lse_chunk) + tails_max);
   }
