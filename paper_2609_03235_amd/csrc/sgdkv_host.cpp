@@ -428,16 +428,18 @@ sgdkv_status plan_compress(const sgdkv_compress_desc* d, int64_t win0, CompressP
     // Rounding up the chunks of every segment can give more than one workgroup per CU (20 segments: 13
     // chunks each, 260): the last, short chunks' workgroups then share the units that the full ones
     // leave, in rounds (with about six tiles' time for their start and tail chunks), after those if
-    // they leave none. Where that takes longer than one chunk less per segment, that is planned instead
-    // (5 sequences of 40000 keys, four heads, 224 / 448 rows: pass 1 57 / 85 us, 84 / 126 otherwise).
+    // they leave none. Where that takes clearly longer than one chunk less per segment, that is planned
+    // instead (5 sequences of 40000 keys, four heads, 224 / 448 rows: pass 1 57 / 85 us, 84 / 126 otherwise).
+    // Not with one row block per wave: there two workgroups and more run on a CU at once, bound by the
+    // memory (12 x 39373 keys x 8 heads, 64 rows of d 64: 104 us, 117 with one chunk less).
     const int64_t nsr = nseg * a.n_rsplit, units = sgdkv::kScoreWorkgroups;
     const int64_t n1 = ceil_div(a.C, a.lse_chunk);
-    if (nsr <= units && nsr * n1 > units) {
+    if (nsr <= units && nsr * n1 > units && a.lse_rs_rows > 16 * sgdkv::kScoreWaves) {
       const int64_t fewer = std::min<int64_t>(round_up(ceil_div(a.C, units / nsr), sgdkv::kScoreChunkQuantum), 1 << 16);
       const int64_t left = units - nsr * (n1 - 1);
       const int64_t last = ceil_div(a.C - (n1 - 1) * a.lse_chunk, sgdkv::kLseTile) + 6;
       const int64_t rounds = left > 0 ? ceil_div(nsr, left) * last : a.lse_chunk / sgdkv::kLseTile + last;
-      if (fewer / sgdkv::kLseTile + 3 < rounds) a.lse_chunk = fewer;
+      if (10 * (fewer / sgdkv::kLseTile + 3) < 9 * rounds) a.lse_chunk = fewer;
     }
     if (tails < sgdkv::kScoreWorkgroups) {
       const int64_t beside = chunk_for(sgdkv::kScoreWorkgroups - tails);
